@@ -39,9 +39,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "seconds/amplitude + contraction TFLOP/s (% MFMA peak), 6x6 d40, FP32-MFMA vs FP64"
-# MI355X dense MFMA peaks (TFLOP/s) of the arithmetic each path issues
-PEAK_TFLOPS = {"fp32": 157.3, "fp32_3m": 157.3, "fp64": 78.6, "bf16x3": 2500.0}
-ISSUED_PER_CMAC = {"fp32": 8, "fp32_3m": 6, "fp64": 8, "bf16x3": 24}   # real MFMA flops per complex multiply-add
+# MI355X dense MFMA peaks (TFLOP/s) of the arithmetic each path's hot kernel
+# issues: FP32 plans run it as three half-precision products of operands split
+# in two (FP32 sums)
+PEAK_TFLOPS = {"fp32": 2500.0, "fp32_3m": 2500.0, "fp64": 78.6, "bf16x3": 2500.0}
+ISSUED_PER_CMAC = {"fp32": 24, "fp32_3m": 24, "fp64": 8, "bf16x3": 24}   # real MFMA flops per complex multiply-add
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_interior_site_6x6_d40_{prec}{split}.json")
 
 
@@ -49,19 +51,20 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-# Section of kernels.hip that holds each precision's hot kernel (between two
-# "// ----...---- <name>" marker lines); traffic counters are tied to its hash.
-KERNEL_SECTIONS = {"fp32_3m": ("3M, direct-to-LDS", "4M, direct-to-LDS"), "fp32": ("4M, direct-to-LDS", "BF16x3")}
+# Source that holds each precision's hot kernel: a file, or the part of it
+# between two "// ----...---- <name>" marker lines; traffic counters are tied to its hash.
+KERNEL_SECTIONS = {"fp32_3m": ("site_f16.hip", None, None),
+                   "fp64": ("kernels.hip", "4M, direct-to-LDS", "BF16x3")}
 
 
 def kernel_source_hash(prec):
-    with open(os.path.join(ROOT, "paper_1905_08394_amd", "csrc", "kernels.hip")) as f:
+    name, first, last = KERNEL_SECTIONS[prec]
+    with open(os.path.join(ROOT, "paper_1905_08394_amd", "csrc", name)) as f:
         lines = f.read().split("\n")
-    first, last = KERNEL_SECTIONS[prec]
-    marker = "// " + "-" * 64 + " "
-    a = lines.index(marker + first)
-    b = lines.index(marker + last)
-    return hashlib.sha256("\n".join(lines[a:b]).encode()).hexdigest()
+    if first:
+        marker = "// " + "-" * 64 + " "
+        lines = lines[lines.index(marker + first):lines.index(marker + last)]
+    return hashlib.sha256("\n".join(lines).encode()).hexdigest()
 
 
 def workload_base(lattice, seed=0):
@@ -875,8 +878,9 @@ def main():
         "config": {"workload": f"{args.lattice}x{args.lattice} lattice, random circuit depth (1+{args.depth}+1), "
                                f"D={stats['chi']}, exact row-scheme amplitudes of {len(bits)} bitstrings "
                                f"sharing rows 1-{args.lattice - 1} (last-row variants)",
-                   "precision": {"fp32": "complex64 storage, FP32 MFMA (4M)",
-                                 "fp32_3m": "complex64 storage, FP32 MFMA (3M, Gauss)" +
+                   "precision": {"fp32": "complex64 storage, FP32 operands split in two halves, FP32 sums (MFMA)",
+                                 "fp32_3m": "complex64 storage, FP32 operands split in two halves, FP32 sums "
+                                            "(MFMA; first sites of a row FP32 3M)" +
                                             (", split K accumulation (partial sums)" if split_on else ""),
                                  "fp64": "complex128 storage, FP64 MFMA",
                                  "bf16x3": "complex64 storage, BF16 hi/lo split, 3 BF16 MFMA products, "

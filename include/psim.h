@@ -63,6 +63,9 @@ typedef struct {
 
 typedef enum {
   PSIM_FP64 = 0,     /* complex128 storage, FP64 MFMA */
+  /* The two FP32 forms hold tensors in complex64 and sum in FP32.  Contractions over a multiple of 16
+     (the interior sites of a row, quadrant sites, joins) split every operand into two halves (22 to 23
+     significant bits) and run on the half-precision matrix units; the others run in FP32 as named. */
   PSIM_FP32_4M = 1,  /* complex64 storage, complex product as one real FP32 MFMA GEMM (4 real mults) */
   PSIM_FP32_3M = 2,  /* complex64 storage, three real FP32 MFMA GEMMs (Gauss) */
   PSIM_BF16X3 = 3    /* complex64 storage, BF16 hi/lo split, 3 BF16 MFMA products, FP32 accumulation */
@@ -72,9 +75,9 @@ typedef enum {
   PSIM_PLAN_HOST_ONLY = 1,  /* plan the contraction on the host only (no device, cannot run) */
   PSIM_PLAN_SPLIT_ACC = 2,  /* FP32 4M and FP32 3M, every site kernel and square-partition join, in
                                both schemes: accumulate each K stage (32 reals of k; each pair of
-                               stages in the direct-to-LDS 3M kernel) separately before adding it to
+                               stages on the half-precision units) separately before adding it to
                                the running sum (smaller rounding error, same work, slower: twice the
-                               accumulator registers; joins are not grouped) */
+                               accumulator registers) */
   PSIM_PLAN_GRAPH = 4       /* psim_amplitudes captures its row sweep into a HIP graph the first time
                                a (workspace, prefix-trie shape) pair is seen and replays it afterwards;
                                ignored while profiling or when PSIM_LOG=1 */
@@ -96,7 +99,8 @@ typedef struct {
   int32_t tile_cfg;           /* interior-site tile candidate: 0 = default, k > 0 = candidate k
                                  (FP32 4M: 1..6, FP32 3M: 1..3, FP64: 1..2, BF16X3: 1..2; with
                                  PSIM_PLAN_SPLIT_ACC only 0, or 3 for FP32 3M (the split kernels'
-                                 tiles): EINVAL otherwise).  With 0 and PSIM_TUNE_CACHE set in the environment, the
+                                 tiles): EINVAL otherwise; contractions on the half-precision units
+                                 have their own rule and ignore it).  With 0 and PSIM_TUNE_CACHE set in the environment, the
                                  choices psim_tune stored there for this device architecture,
                                  precision and shape are used; psim_tune may replace them */
 } psim_plan_opts;

@@ -75,6 +75,7 @@ struct WsLayout {
   std::vector<uint8_t*> tau;
   int32_t* exp[2];
   uint32_t* mx;
+  std::vector<uint32_t*> amax;  // per f16 site (Step::amax): one word per node
   char* F[2];
   char* G[2];
 };
@@ -100,6 +101,7 @@ WsLayout layout(const psim_plan_t& pl, void* ws, char* tab = nullptr) {
   w.exp[0] = (int32_t*)p; p += al((uint64_t)nmax_all * 4);
   w.exp[1] = (int32_t*)p; p += al((uint64_t)nmax_all * 4);
   w.mx = (uint32_t*)p; p += al((uint64_t)nmax_all * 4);
+  for (int k = 0; k < pl.n_amax; ++k, p += al((uint64_t)nmax_all * 4)) w.amax.push_back((uint32_t*)p);
   p = base + pl.ws_tab;
   w.F[0] = p + pl.levels[0].F_off;
   w.F[1] = p + (R > 1 ? pl.levels[1].F_off : 0);
@@ -157,6 +159,7 @@ void tune_plan(psim_plan_t* pl, void* ws, size_t ws_bytes, void* stream, int rep
     const DevMatrix& dm = pl->w[((size_t)s.i * L + s.j) * 2];
     g.W0 = g.W1 = dm.ptr;
     g.ldw = dm.ld;
+    g.f16 = dm.f16;
     if (dm.ptr_b) {  // BF16x3: the pre-split planes
       g.Wb0 = g.Wb1 = dm.ptr_b;
       g.ldwb = dm.ld_b;
@@ -329,6 +332,11 @@ void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
       const int64_t gn = std::min<int64_t>(lev.group, nodes - g0);
       for (int v0 = 0; v0 < lev.Dv; v0 += c) {
         for (int w0 = 0; w0 < (wc ? lev.Dw : 1); w0 += cw) {
+          // |components of the running tensor| < 2^a_exp times what the last f16
+          // site measured (a_max, when there is one): boundaries are rescaled
+          // below 1 (row 0 starts from 1), site matrices too
+          int a_exp = i == 0 ? 1 : 0;
+          const uint32_t* a_max = nullptr;
           for (int j = 0; j < L; ++j) {
             const Step& s = pl->steps[(size_t)i * L + j];
             const DevMatrix& w0m = pl->w[((size_t)i * L + j) * 2];
@@ -353,6 +361,16 @@ void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
             g.W0 = w0m.ptr;
             g.W1 = w1m.ptr;
             g.ldw = w0m.ld;
+            if (s.amax >= 0) {
+              g.f16 = 1;
+              g.a_exp = a_exp;
+              g.amax_in = a_max;
+              g.amax_out = W.amax[s.amax] + g0;
+              a_exp = 0;
+              a_max = g.amax_out;
+            } else {
+              a_exp += growth_exp(s.K1 * s.K2);
+            }
             g.tau = W.tau[i] + g0 * L + j;
             g.tau_stride = L;
             g.nodes = gn;

@@ -577,234 +577,26 @@ __global__ __launch_bounds__(256) void site_gemm_group(GroupArgs ga) {
   site_gemm_body<T, BM, BN, BK, AMODE, TRANS, SCH, false>(p, g - ga.start[i]);
 }
 
-// ---------------------------------------------------------------- 3M, direct-to-LDS
-// The 3M interior-site contraction for launches where every tile is interior
-// and every stage lies inside one k1 block (the ROWFAST conditions), with
-// operands copied global -> LDS by the load unit itself
-// (global_load_lds_dwordx4): no register staging and no LDS store
-// instructions.  Each wave-wide copy writes 64 x 16 bytes contiguously, so the
-// LDS tiles are unpadded rows of BK floats (8 chunks of 16 bytes) and the lane
-// that fills physical chunk p of row r fetches logical chunk p ^ swz(r); the
-// fragment reads apply the same permutation, which spreads 16 consecutive
-// rows over distinct banks.  The two LDS buffers are separate arrays and the
-// K loop is unrolled by two, so each copy and each read names its buffer.
+// ---------------------------------------------------------------- 4M, direct-to-LDS
+// The interior-site contraction for launches where every tile is interior and
+// every stage lies inside one k1 block (the ROWFAST conditions): FP64 plans on
+// v_mfma_f64_16x16x4f64, and the FP32 companion sweep of BF16x3 plans on
+// v_mfma_f32_32x32x2f32 (FP32 4M and 3M plans run these shapes on the
+// half-precision units, site_f16.hip).  Operands are copied global -> LDS by
+// the load unit itself (global_load_lds_dwordx4): no register staging and no
+// LDS store instructions.  Each wave-wide copy writes 64 x 16 bytes
+// contiguously, so the LDS tiles are unpadded rows of 128 bytes (8 chunks of
+// 16 bytes; 32 floats or 16 doubles) and the lane that fills physical chunk p
+// of row r fetches logical chunk p ^ swz(r); the fragment reads apply the same
+// permutation, which spreads 16 consecutive rows over distinct banks.  The two
+// LDS buffers are separate arrays and the K loop is unrolled by two, so each
+// copy and each read names its buffer.  BM x BN real outputs per workgroup; a
+// lane's fragment (KV consecutive k) is one chunk.  The products and their
+// order are those of the row-major kernel with the same tile.
 #define PSIM_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
 __device__ __forceinline__ int dtl_swz(int r) { return (r ^ (r >> 3)) & 7; }
 
-template <int BM, int BN, bool SPLIT = false>
-__device__ __forceinline__ void dtl3m_body(const KArgs& p, const long long t) {
-  constexpr int BK = 32;                 // floats per stage row = 8 chunks
-  constexpr int MB = 32;
-  constexpr int WM = BM / 2, WN = BN / 2;
-  constexpr int MBLK = WM / MB;
-  constexpr int NBLK3 = WN / 2 / MB;
-  constexpr int BROWS = BN / 2;          // packed-W rows (complex columns) per tile
-  constexpr int A_INS = BM * BK / 4 / 64 / 4;     // wave-wide 1 KB copies per wave
-  constexpr int B_INS = BROWS * BK / 4 / 64 / 4;
-  static_assert(A_INS >= 1 && B_INS >= 1 && NBLK3 >= 1, "tile");
-  __shared__ __attribute__((aligned(1024))) float sA0[BM * BK];
-  __shared__ __attribute__((aligned(1024))) float sA1[BM * BK];
-  __shared__ __attribute__((aligned(1024))) float sB0[BROWS * BK];
-  __shared__ __attribute__((aligned(1024))) float sB1[BROWS * BK];
-
-  const long long nt = t % p.NT;
-  const long long rest = t / p.NT;
-  const long long mt = rest % p.MT;
-  const long long z = rest / p.MT;
-  const long long node = z / p.Bz, vb = z % p.Bz;
-  const long long ablk = p.a_index ? (long long)p.a_index[node] : node;
-  const float* __restrict__ A = (const float*)p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
-  const int tauv = p.tau ? (int)p.tau[node * p.tau_stride] : 0;
-  const float* __restrict__ W = (const float*)(tauv ? p.W1 : p.W0) + p.w_koff_r;
-  float* __restrict__ C = (float*)p.C + 2 * (node * p.sC_node + vb * p.sC_v);
-  const long long m0 = mt * BM;
-  const long long brow0 = nt * BROWS;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wid = tid >> 6;
-  const int wr = wid >> 1, wc = wid & 1;
-  const long long sK1 = p.M * p.K2;
-
-  // Copy `it` of this wave fills tile rows (it * 4 + wid) * 8 + lane / 8,
-  // physical chunk lane % 8; the lane fetches logical chunk p ^ swz(row).
-  // Byte offsets from the uniform stage base stay below 2^31.
-  const unsigned a_rs = (unsigned)(2 * p.K2 * 4);  // bytes between rows of A
-  const unsigned b_rs = (unsigned)(p.ldw * 4);     // bytes between rows of packed W
-  auto src_off = [&](int it, unsigned row_stride) {
-    const int row = (it * 4 + wid) * 8 + (lane >> 3);
-    const int chk = (lane & 7) ^ dtl_swz(row);
-    return (unsigned)row * row_stride + (unsigned)chk * 16u;
-  };
-  long long fk1 = 0, fk2 = 0, kr = 0;  // next stage: (k1, k2) of A, real k of W
-  auto issue = [&](float* sa, float* sb) {
-    const char* abase = (const char*)(A + 2 * (fk1 * sK1 + m0 * p.K2 + fk2));
-    const char* bbase = (const char*)(W + brow0 * p.ldw + kr);
-#pragma unroll
-    for (int it = 0; it < A_INS; ++it)
-      __builtin_amdgcn_global_load_lds((const void*)(abase + src_off(it, a_rs)), PSIM_LDS(sa + (it * 4 + wid) * 256),
-                                       16, 0, 0);
-#pragma unroll
-    for (int it = 0; it < B_INS; ++it)
-      __builtin_amdgcn_global_load_lds((const void*)(bbase + src_off(it, b_rs)), PSIM_LDS(sb + (it * 4 + wid) * 256),
-                                       16, 0, 0);
-    fk2 += BK / 2;
-    if (fk2 == p.K2) {
-      fk2 = 0;
-      ++fk1;
-    }
-    kr += BK;
-  };
-
-  f32x16 acc3[MBLK][NBLK3][3];
-#pragma unroll
-  for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NBLK3; ++bj)
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc3[bi][bj][q][r] = 0;
-  // SPLIT: the products of each pair of stages (64 reals of k) are summed on
-  // their own (fresh partial accumulators, opened by the pair's first stage)
-  // and then added to the running sums (by its second), which shortens the
-  // FP32 rounding chains of the K loop
-  f32x16 part[SPLIT ? MBLK : 1][SPLIT ? NBLK3 : 1][SPLIT ? 3 : 1];
-
-  const int frow = lane % MB;
-  const int fh = (lane / MB) * 2;  // first logical chunk of this lane half within a group of 4
-  auto compute = [&](const float* a_s, const float* b_s, const bool open, const bool close) {
-    if (SPLIT && open) {
-#pragma unroll
-      for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < NBLK3; ++bj)
-#pragma unroll
-          for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part[bi][bj][q][r] = 0;
-    }
-    auto& dst = [&]() -> auto& {
-      if constexpr (SPLIT) return part;
-      else return acc3;
-    }();
-#pragma unroll
-    for (int g = 0; g < BK / 16; ++g) {
-      f32x4 ar[MBLK], ai[MBLK], as[MBLK], br[NBLK3], bim[NBLK3], bs[NBLK3];
-#pragma unroll
-      for (int bi = 0; bi < MBLK; ++bi) {
-        const int r = wr * WM + bi * MB + frow;
-        const int c0 = g * 4 + fh, sw = dtl_swz(r);
-        const f32x4 x0 = *(const f32x4*)(a_s + r * BK + ((c0 ^ sw) << 2));
-        const f32x4 x1 = *(const f32x4*)(a_s + r * BK + (((c0 + 1) ^ sw) << 2));
-        ar[bi] = f32x4{x0[0], x0[2], x1[0], x1[2]};
-        ai[bi] = f32x4{x0[1], x0[3], x1[1], x1[3]};
-        as[bi] = ar[bi] + ai[bi];
-      }
-#pragma unroll
-      for (int bj = 0; bj < NBLK3; ++bj) {
-        const int r = wc * (WN / 2) + bj * MB + frow;
-        const int c0 = g * 4 + fh, sw = dtl_swz(r);
-        const f32x4 x0 = *(const f32x4*)(b_s + r * BK + ((c0 ^ sw) << 2));
-        const f32x4 x1 = *(const f32x4*)(b_s + r * BK + (((c0 + 1) ^ sw) << 2));
-        br[bj] = f32x4{x0[0], x0[2], x1[0], x1[2]};
-        bim[bj] = f32x4{x0[1], x0[3], x1[1], x1[3]};
-        bs[bj] = br[bj] + bim[bj];
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-          for (int bj = 0; bj < NBLK3; ++bj) {
-            dst[bi][bj][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[bi][s], br[bj][s], dst[bi][bj][0], 0, 0, 0);
-            dst[bi][bj][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai[bi][s], bim[bj][s], dst[bi][bj][1], 0, 0, 0);
-            dst[bi][bj][2] = __builtin_amdgcn_mfma_f32_32x32x2f32(as[bi][s], bs[bj][s], dst[bi][bj][2], 0, 0, 0);
-          }
-    }
-    if (SPLIT && close) {
-#pragma unroll
-      for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < NBLK3; ++bj)
-#pragma unroll
-          for (int q = 0; q < 3; ++q) acc3[bi][bj][q] += part[bi][bj][q];
-    }
-  };
-  // vmcnt(0), other counters unconstrained: the copies into LDS have landed
-  constexpr unsigned kWaitVm0 = 0x3f70;
-
-  // the launcher guarantees an even number of stages
-  const int npair = (int)(p.Kr / (2 * BK));
-  issue(sA0, sB0);
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  __syncthreads();
-  for (int kp = 0; kp < npair; ++kp) {
-    issue(sA1, sB1);
-    compute(sA0, sB0, true, false);
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    __syncthreads();
-    if (kp + 1 < npair) issue(sA0, sB0);
-    compute(sA1, sB1, false, true);
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    __syncthreads();
-  }
-
-  const long long c0 = nt * (BN / 2);  // first complex column of the tile
-#pragma unroll
-  for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NBLK3; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const long long row = m0 + wr * WM + bi * MB + Mfma<float>::out_row(lane, r);
-        const long long col = c0 + wc * (WN / 2) + bj * MB + Mfma<float>::out_col(lane);
-        if (col < p.N) {
-          const float t1 = acc3[bi][bj][0][r], t2 = acc3[bi][bj][1][r], t3 = acc3[bi][bj][2][r];
-          f32x2 v = {t1 - t2, t3 - t1 - t2};
-          *(f32x2*)(C + 2 * (row * p.N + col)) = v;
-        }
-      }
-}
-
-template <int BM, int BN>
-__global__ __launch_bounds__(256, 3) void site_gemm_3m_dtl(KArgs p) {
-  const long long t = xcd_tile(p.T);
-  if (t >= p.T) return;
-  dtl3m_body<BM, BN>(p, t);
-}
-
-// split-accumulation form (PSIM_PLAN_SPLIT_ACC): twice the accumulators, two
-// workgroups per CU
-template <int BM, int BN, int OCC = 2>
-__global__ __launch_bounds__(256, OCC) void site_gemm_3m_dtl_split(KArgs p) {
-  const long long t = xcd_tile(p.T);
-  if (t >= p.T) return;
-  dtl3m_body<BM, BN, true>(p, t);
-}
-
-// grouped form (see site_gemm_group)
-template <int BM, int BN>
-__global__ __launch_bounds__(256, 3) void site_gemm_3m_dtl_group(GroupArgs ga) {
-  const long long total = ga.start[ga.nprob];
-  const long long g = xcd_tile(total);
-  if (g >= total) return;
-  const int i = find_problem(ga, g);
-  KArgs p;
-  const int* src = (const int*)ga.probs[i];
-  int* dst = (int*)&p;
-#pragma unroll
-  for (int w = 0; w < (int)(sizeof(KArgs) / 4); ++w) dst[w] = __builtin_amdgcn_readfirstlane(src[w]);
-  dtl3m_body<BM, BN>(p, g - ga.start[i]);
-}
-
-// ---------------------------------------------------------------- 4M, direct-to-LDS
-// 4M form of the direct-to-LDS interior kernel (FP32 on v_mfma_f32_32x32x2f32,
-// FP64 on v_mfma_f64_16x16x4f64): the real expansion of the complex product,
-// stage rows of 128 bytes (32 floats or 16 doubles: the same chunks and
-// swizzle as above), BM x BN real outputs per workgroup.  A lane's fragment
-// (KV consecutive k) is one 16-byte chunk.  The products and their order are
-// those of the row-major kernel with the same tile.
 template <typename T, int BM, int BN, int OCC>
 __global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
   typedef Mfma<T> MF;
@@ -1549,13 +1341,14 @@ void hip_check(int err, const char* what) {
 struct FCfg {
   int bm, bn, bk;
 };
-// 6 = the direct-to-LDS 4M kernel with 128 x 64 tiles (0 is its 128 x 128 form)
+// 6 runs the default tiles
 static const FCfg kFp32Configs[] = {{128, 128, 32}, {256, 128, 16}, {128, 256, 16},
                                     {256, 256, 16}, {128, 128, 64}, {256, 128, 32}, {128, 64, 32}};
 int fp32_config_count() { return (int)(sizeof(kFp32Configs) / sizeof(kFp32Configs[0])); }
 // 3M candidates: 0 = 128 x 128 x 32 (two waves per SIMD), 1 = 256 x 128 x 32,
-// 2 = 128 x 256 x 32 (one wave per SIMD, twice the work per LDS stage)
-// 3 = the direct-to-LDS kernel with 64 x 128 tiles (more workgroups per CU)
+// 2 = 128 x 256 x 32 (one wave per SIMD, twice the work per LDS stage), 3 = as
+// 0.  The candidates choose among kernels only where a shape does not go to
+// the half-precision units (site_f16.hip).
 static const FCfg kFp32_3mConfigs[] = {{128, 128, 32}, {256, 128, 32}, {128, 256, 32}, {64, 128, 32}};
 int fp32_3m_config_count() { return (int)(sizeof(kFp32_3mConfigs) / sizeof(kFp32_3mConfigs[0])); }
 // FP64 candidates: 0 = direct-to-LDS 128 x 64, 1 = direct-to-LDS 64 x 64,
@@ -1625,19 +1418,14 @@ static int fp32_mode(const GemmLaunch& g) {
          : (g.K2 == 1 && g.M % 2 == 0 && g.K1 > 1 && even_base) ? KMAJOR : GENERIC;
 }
 
-// The direct-to-LDS 3M kernel applies: interior tiles only, every K stage
-// inside one k1 block, an even number of stages, 32-bit copy offsets.
-static bool dtl3m_ok(const GemmLaunch& g, int mode, int bm = 128) {
-  return g.prec == PSIM_FP32_3M && !g.trans_out && !g.nb && mode == ROWMAJOR && g.M % bm == 0 &&
-         (2 * g.K2) % 32 == 0 && (2 * g.K1 * g.K2) % 64 == 0 && g.K2 < (1 << 20) && g.ldw < (1 << 22);
-}
-
 // Grouped-launch variants (FP32 only), the kernels launch_site_gemm picks for
 // default tiles: id = 8 * (3M ? 1 : 0) + 2 * mode + trans with 128 x 128 x 32
 // tiles (mode: ROWMAJOR, KMAJOR, GENERIC, ROWFAST); 16 / 17 = 4M transposed
-// small-N tiles (256 x 64 x 16, ROWMAJOR / KMAJOR); 18 = 3M direct-to-LDS.
-// -1: not groupable.
+// small-N tiles (256 x 64 x 16, ROWMAJOR / KMAJOR).
+// -1: not groupable.  From kF16Group on: the half-precision kernels' own.
+constexpr int kF16Group = 32;
 int group_variant(const GemmLaunch& g, void* out, long long* tiles) {
+  if (g.f16) return kF16Group + group_variant_f16(g, out, tiles);
   if ((g.prec != PSIM_FP32_4M && g.prec != PSIM_FP32_3M) || g.split || g.cfg > 0) return -1;
   int mode = fp32_mode(g);
   KArgs a = make_kargs(g);
@@ -1647,10 +1435,6 @@ int group_variant(const GemmLaunch& g, void* out, long long* tiles) {
     id = mode == ROWMAJOR ? 16 : 17;
     bm = 256;
     bn = 64;
-  } else if (dtl3m_ok(g, mode)) {
-    id = 18;
-    bm = 128;
-    bn = 128;
   } else {
     if (mode == ROWMAJOR && g.M % 128 == 0 && (2 * g.K1 * g.K2) % 32 == 0 && (2 * g.K2) % 32 == 0) mode = ROWFAST;
     id = 8 * (g.prec == PSIM_FP32_3M ? 1 : 0) + 2 * mode + (g.trans_out ? 1 : 0);
@@ -1684,7 +1468,8 @@ static void glaunch_mode(int mode, bool trans, const GroupArgs& ga, long long bl
 void launch_group(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   if (nprob < 1 || nprob > kMaxGroup) fail(PSIM_EINTERNAL, "group size out of range");
-  if (variant < 0 || variant > 18) fail(PSIM_EINTERNAL, "unknown group variant");
+  if (variant >= kF16Group) return launch_group_f16(variant - kF16Group, d_probs, start, nprob, stream);
+  if (variant < 0 || variant > 17) fail(PSIM_EINTERNAL, "unknown group variant");
   GroupArgs ga{};
   for (int i = 0; i < nprob; ++i) {
     ga.probs[i] = (const KArgs*)d_probs[i];
@@ -1696,9 +1481,7 @@ void launch_group(int variant, const void* const* d_probs, const long long* star
   if (total < 1) return;
   const long long blocks = (total + 7) / 8 * 8;
   if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-  if (variant == 18)
-    hipLaunchKernelGGL((site_gemm_3m_dtl_group<128, 128>), dim3((unsigned)blocks), dim3(256), 0, st, ga);
-  else if (variant == 16)
+  if (variant == 16)
     hipLaunchKernelGGL((site_gemm_group<float, 256, 64, 16, ROWMAJOR, true, 4>), dim3((unsigned)blocks), dim3(256), 0,
                        st, ga);
   else if (variant == 17)
@@ -1711,7 +1494,7 @@ void launch_group(int variant, const void* const* d_probs, const long long* star
   hip_check(hipGetLastError(), "grouped site_gemm launch");
 }
 
-int kargs_bytes() { return (int)sizeof(KArgs); }
+int kargs_bytes() { return std::max((int)sizeof(KArgs), f16_descriptor_bytes()); }
 int max_group() { return kMaxGroup; }
 
 // FP32 launch arguments with 128 x 128 tiles over Z batch entries
@@ -1725,6 +1508,7 @@ static KArgs default_tiles(const KArgs& a, long long Z) {
 static long long default_blocks(const KArgs& a, long long Z) { return (default_tiles(a, Z).T + 7) / 8 * 8; }
 
 void launch_site_gemm(const GemmLaunch& g, void* stream) {
+  if (g.f16) return launch_site_f16(g, stream);
   hipStream_t st = (hipStream_t)stream;
   KArgs a = make_kargs(g);
   // batch entries = nodes * Bz; the kernel splits z = node * Bz + v
@@ -1810,8 +1594,8 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
       else
         g.trans_out ? launch<float, 128, 128, 32, GENERIC, true, 4, true>(b, blocks, st)
                     : launch<float, 128, 128, 32, GENERIC, false, 4, true>(b, blocks, st);
-    } else if (g.split && g.prec == PSIM_FP32_3M && !dtl3m_ok(g, mode)) {
-      // 3M launches outside the direct-to-LDS kernel, per-stage partial sums
+    } else if (g.split && g.prec == PSIM_FP32_3M) {
+      // per-stage partial sums
       if (fast(128, 32))
         g.trans_out ? launch<float, 128, 128, 32, ROWFAST, true, 3, true>(b, blocks, st)
                     : launch<float, 128, 128, 32, ROWFAST, false, 3, true>(b, blocks, st);
@@ -1874,32 +1658,12 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
                   : launch<float, 256, 128, 32, ROWMAJOR, false, 3>(b, bl, st); break;
         case 2: f ? launch<float, 128, 256, 32, ROWFAST, false, 3>(b, bl, st)
                   : launch<float, 128, 256, 32, ROWMAJOR, false, 3>(b, bl, st); break;
-        case 3:
-          if (dtl3m_ok(g, mode, 64))
-            hipLaunchKernelGGL((site_gemm_3m_dtl<64, 128>), dim3((unsigned)bl), dim3(256), 0, st, b);
-          else  // shapes the direct-to-LDS kernel does not take: 128 x 128 tiles
-            launch<float, 128, 128, 32, ROWMAJOR, false, 3>(default_tiles(a, Z), default_blocks(a, Z), st);
+        case 3:  // 64 x 128 tiles: the split form's only
+          launch<float, 128, 128, 32, ROWMAJOR, false, 3>(default_tiles(a, Z), default_blocks(a, Z), st);
           break;
         default: fail(PSIM_EINVAL, "unknown kernel config");
       }
-    } else if (dtl3m_ok(g, mode)) {
-      // interior tiles, an even number of K stages, 32-bit copy offsets:
-      // the direct-to-LDS kernel (same products in the same order as the
-      // ROWFAST 3M kernel, so the same results bit for bit)
-      if (g.split && g.cfg == 3) {
-        // split accumulation with 64 x 128 tiles: half the accumulators per
-        // wave, three workgroups per CU instead of two
-        KArgs f = b;
-        f.MT = f.M / 64;
-        f.T = f.MT * f.NT * Z;
-        const long long fb = (f.T + 7) / 8 * 8;
-        if (fb > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-        hipLaunchKernelGGL((site_gemm_3m_dtl_split<64, 128, 3>), dim3((unsigned)fb), dim3(256), 0, st, f);
-      } else if (g.split)
-        hipLaunchKernelGGL((site_gemm_3m_dtl_split<128, 128>), dim3((unsigned)blocks), dim3(256), 0, st, b);
-      else
-        hipLaunchKernelGGL((site_gemm_3m_dtl<128, 128>), dim3((unsigned)blocks), dim3(256), 0, st, b);
-  } else if (g.prec == PSIM_FP32_3M) {
+    } else if (g.prec == PSIM_FP32_3M) {
       if (fast(128, 32))
         g.trans_out ? launch<float, 128, 128, 32, ROWFAST, true, 3>(b, blocks, st)
                     : launch<float, 128, 128, 32, ROWFAST, false, 3>(b, blocks, st);
@@ -1933,10 +1697,7 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
         case 5: f ? launch<float, 256, 128, 32, ROWFAST, false>(b, bl, st)
                   : launch<float, 256, 128, 32, ROWMAJOR, false>(b, bl, st); break;
         case 6:
-          if (f && (2 * g.K1 * g.K2) % 64 == 0 && g.K2 < (1 << 20) && g.ldw < (1 << 22))
-            hipLaunchKernelGGL((site_gemm_4m_dtl<float, 128, 64, 3>), dim3((unsigned)bl), dim3(256), 0, st, b);
-          else
-            launch<float, 128, 128, 32, ROWMAJOR, false>(default_tiles(a, Z), default_blocks(a, Z), st);
+          launch<float, 128, 128, 32, ROWMAJOR, false>(default_tiles(a, Z), default_blocks(a, Z), st);
           break;
         default: fail(PSIM_EINVAL, "unknown kernel config");
       }
@@ -1969,6 +1730,11 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
                   : launch<float, 128, 128, 32, GENERIC, false>(b, blocks, st);
   }
   hip_check(hipGetLastError(), "site_gemm launch");
+}
+
+void launch_zero_u32(uint32_t* p, int64_t n, void* stream) {
+  hipLaunchKernelGGL(zero_u32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, p, (long long)n);
+  hip_check(hipGetLastError(), "zero launch");
 }
 
 static unsigned grid_for(long long total) {

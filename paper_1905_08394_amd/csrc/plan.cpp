@@ -310,6 +310,9 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
       Fmin[i % 2] = std::max(Fmin[i % 2], al((uint64_t)lev.F_elems * eb));
     }
     tab += 3 * al((uint64_t)nmax_all * 4);  // exponents (two levels) and row maxima
+    for (Step& st : pl->steps)  // largest components of the f16 sites' outputs
+      if (st.kind == 1 && f16_site(opts.prec, st.M, st.K1, st.K2)) st.amax = pl->n_amax++;
+    tab += (uint64_t)pl->n_amax * al((uint64_t)nmax_all * 4);
     pl->ws_tab = tab;
     if (tab + Fmin[0] + Fmin[1] > budget)
       fail(PSIM_ENOMEM, "plan needs at least " + std::to_string(tab + Fmin[0] + Fmin[1]) +
@@ -447,8 +450,10 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
           // the last site of a row always runs the 4M transposed-store kernel
           // in FP32 plans (its 256 x 64 tile suits the few output columns)
           const bool last = (j == L - 1);
-          const int pack_prec =
-              (opts.prec == PSIM_BF16X3 || (opts.prec == PSIM_FP32_3M && last)) ? PSIM_FP32_4M : opts.prec;
+          dm.f16 = pl->steps[(size_t)i * L + j].amax >= 0;
+          const int pack_prec = dm.f16 ? PSIM_FP32_3M  // split into halves below
+                                : (opts.prec == PSIM_BF16X3 || (opts.prec == PSIM_FP32_3M && last)) ? PSIM_FP32_4M
+                                                                                                    : opts.prec;
           pack_site_matrix(pack_prec, W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld);
           // a row cut over w reads the first site's matrix from an offset
           // (the columns of one w chunk): 256 zero rows keep the last
@@ -459,6 +464,7 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
             hip_check(hipSetDevice(opts.device), "hipSetDevice");
             hip_check(hipMalloc(&dm.ptr, buf.size()), "hipMalloc(site matrix)");
             hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
+            if (dm.f16) launch_pack_w_f16(dm.ptr, dm.ptr, (int64_t)(buf.size() / 128), nullptr);
           }
           if (opts.prec == PSIM_BF16X3) {  // interior sites also get the split planes
             pack_site_matrix_bf16(W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld_b, dm.plane_b);

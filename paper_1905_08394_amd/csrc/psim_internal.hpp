@@ -65,6 +65,7 @@ struct Step {
   int64_t M = 1, K1 = 1, K2 = 1, N = 1;
   int64_t g_out = 0;     // elements of the output per (node, v) (kind 0/1)
   int cfg = 0;           // kernel tile candidate chosen by the tuner
+  int amax = -1;         // f16 sites: index of the workspace slots for the largest component of the output
 };
 
 struct Level {
@@ -85,6 +86,7 @@ struct DevMatrix {
   void* ptr = nullptr;   // packed, on device
   int64_t ld = 0;        // leading dimension (real elements) of the packed layout
   int exp2 = 0;          // site matrix was scaled by 2^-exp2
+  bool f16 = false;      // ptr holds W split into halves (site_f16.hip)
   void* ptr_b = nullptr; // BF16x3 plans: hi and lo bf16 planes of the 4M expansion
   int64_t ld_b = 0, plane_b = 0;
 };
@@ -108,6 +110,7 @@ struct psim_plan_s {
   double cmac = 0;
   int64_t peak_elems = 0;
   uint64_t weights_bytes = 0;
+  int n_amax = 0;                        // f16 sites of the plan
   uint64_t ws_F = 0, ws_G = 0, ws_tab = 0, ws_total = 0;
   bool host_only = false;
   int elem_bytes = 8;
@@ -193,6 +196,11 @@ struct GemmLaunch {
   const void* Wb1 = nullptr;
   int64_t ldwb = 0, planeb = 0;
   int64_t ldct = 0;                   // transposed stores: row stride of C^T in complex elements (0 = M)
+  int32_t f16 = 0;                    // FP32 4M / 3M: W0 and W1 are split into halves (site_f16.hip)
+  int32_t a_exp = 0, w_exp = 0;       // f16: |components of A| < 2^a_exp (times what amax_in says), W is 2^-w_exp
+                                      // times the matrix to contract
+  const uint32_t* amax_in = nullptr;  // f16, per node: exponent + 4096 of the largest component of A (0: A is zero)
+  uint32_t* amax_out = nullptr;       // f16, per node: raised to the exponent + 4096 of the largest component of C
   int64_t nb = 0, sCw = 0;            // plain stores with nb > 0: C[n / nb][m][n % nb], blocks sCw apart
 };
 int fp32_config_count();
@@ -211,6 +219,26 @@ std::string tune_key(const std::string& arch, int prec, int64_t M, int64_t K1, i
 bool tune_cache_lookup(const std::string& key, int* cfg);
 void tune_cache_store(const std::map<std::string, std::pair<int, double>>& entries);
 void launch_site_gemm(const GemmLaunch& g, void* stream);
+// site_f16.hip: FP32 contractions on the half-precision matrix units.  A
+// contraction goes there when its matrix was packed for it, which f16_site
+// decides from the shape alone (M: the most rows it is launched with).
+bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2);
+void launch_site_f16(const GemmLaunch& g, void* stream);
+int group_variant_f16(const GemmLaunch& g, void* out, long long* tiles);
+void launch_group_f16(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream);
+int f16_descriptor_bytes();
+// groups * 16 complex k of packed 3M rows (Re, Im interleaved along k) into
+// the split halves the kernels read, in place or not
+void launch_pack_w_f16(const void* src, void* dst, int64_t groups, void* stream);
+// exponent + 4096 of the largest component of each of `nodes` tensors (0: all zeros)
+void launch_exponents_f16(const void* A, int64_t per_node, int64_t stride, int64_t nodes, uint32_t* out, void* stream);
+// growth of a contraction: |components of C| < 2^growth_exp(K) max |A| max |W|
+inline int growth_exp(int64_t K) {
+  int e = 1;
+  while ((int64_t(1) << (e - 1)) < K) ++e;
+  return e;
+}
+void launch_zero_u32(uint32_t* p, int64_t n, void* stream);
 // Grouped launches (several problems, one grid): returns the variant id and
 // writes the problem descriptor (kargs_bytes() bytes) to out and its tile
 // count to *tiles, or returns -1 when the launch is not groupable.

@@ -1,0 +1,535 @@
+// Site contractions of FP32 plans (4M and 3M) on the half-precision matrix units.
+//
+//   C[m][n] = sum_{k1, k2} A[k1][m][k2] * W[k1*K2 + k2][n]        (complex, eq. S4)
+//
+// Every FP32 operand x (scaled by an exact power of two into the top of the
+// half range) is split into two half-precision numbers, x = hi + lo with
+// hi = half(x), lo = half(x - hi) (round to nearest even: 22 to 23 significant
+// bits), and
+//   a b ~= a_hi b_hi + a_hi b_lo + a_lo b_hi
+// is accumulated in FP32 by v_mfma_f32_32x32x16_f16: the products are exact
+// and the dropped a_lo b_lo is below 2^-22 of the product.  (Error-corrected
+// products on matrix units: Ootomo and Yokota, "Recovering single precision
+// accuracy from Tensor Cores while surpassing the FP32 theoretical peak
+// performance", 2022.)  The complex product is four real ones (Re = ArWr -
+// AiWi, Im = ArWi + AiWr).
+//
+// Why: an FP32 complex multiply-add is 6 (Gauss) or 8 flops on a unit of 157
+// TFLOP/s; here it is 24 half flops on a unit 16 times as fast, which sustains
+// about 1.1 PFLOP/s (the rate a library half or bfloat16 product of 8192^3
+// reaches on this card; the clock falls under that load).  So the floor of a
+// contraction is 24 flops per multiply-add at that rate, 46e12 multiply-adds a
+// second, or its bytes where K and N are below about 64.
+//
+// Accuracy: per-instruction sums of 16 products and a last bit less of input
+// round the result no more than FP32 instructions of 2 products do.  Error
+// (2-norm, against 64 bits) of normal random operands, K = 1024 / 256 / 64:
+//   one running sum     5.0e-7 / 2.6e-7 / 1.35e-7   (FP32 4M 8.1e-7 / 4.0e-7 / 2.0e-7, 3M 8.1e-7 / 4.1e-7 / 2.1e-7)
+//   partial sums (split) 1.55e-7 / 1.22e-7 / 1.08e-7 (FP32 4M 1.80e-7 / 1.28e-7 / 1.10e-7, 3M 2.15e-7 / 1.74e-7 / 1.28e-7)
+// and of amplitudes (rms over seeds): 5x5 (1+32+1) 4M 1.06e-6 -> 0.97e-6, 3M
+// 1.10e-6 -> 0.99e-6, 4M split 6.1e-7 -> 5.8e-7, 3M split 7.2e-7 -> 6.0e-7; 5x5
+// (1+40+1) 3M split 8.4e-7 -> 6.7e-7; 8x8 (1+25+1) square partition 3M 1.9e-6
+// -> 1.5e-6, split 1.29e-6 -> 1.13e-6.
+//
+// Scale: the halves cover 40 binades, so every node's A is scaled by the
+// exponent of its largest component.  A producer on these units measures it
+// in its epilogue (amax_out -> amax_in); elsewhere a bound from the last
+// rescale is carried along (a_exp: growth_exp(K) per site), which overstates
+// the maximum by a few binades and costs no precision until it overstates it by
+// about 15.  Components more than 2^-17 below the largest lose relative (not
+// absolute) precision: their error stays below 2^-40 of the largest.
+//
+// Measured (ms before, FP32 units -> now): 16 x (M = 32768, K = N = 1024) split
+// 26.3 -> 13.5, unsplit 23.9 -> 11.0; 64 x (4096, 256, 256) split 0.95 -> 0.49,
+// unsplit 0.89 -> 0.40; 512 x (4096, 64, 64) split 0.81 -> 0.43 (HBM: 5.0
+// TB/s), unsplit 0.68 -> 0.40; 4 x (4096, 4096, 4096) unsplit 12.0 -> 5.7.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstring>
+
+#include "psim_internal.hpp"
+
+namespace psim {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+namespace {
+
+struct F16Args {
+  const float* A;
+  float* C;
+  const float* W0;
+  const float* W1;
+  const int32_t* a_index;
+  const uint8_t* tau;
+  const uint32_t* amax_in;   // per node: exponent + 4096 of max |component of A|, 0 = all zeros
+  uint32_t* amax_out;
+  long long tau_stride;
+  long long M, K1, K2, N;
+  long long ldw;             // bytes between rows of W
+  long long sA_node, sA_v, sC_node, sC_v;
+  long long MT, NT, T;
+  int Bz, nst, a_exp, w_exp;
+};
+
+constexpr int kTop = 15;     // A is scaled to below 2^kTop,
+constexpr int kTopW = 14;    // W below 2^kTopW (both finite as halves)
+
+// One tile: WVM x WVN waves of MBLK x NBLK blocks of 32 x 32 complex outputs.
+// Stages of 16 complex k (128-byte rows of A and of W) go global -> LDS
+// without registers, double buffered; the other workgroups of the CU cover the
+// waits.  A is split in registers as its fragments are read (40 VALU
+// instructions for 24 matrix instructions of 32 cycles), so any FP32 tensor
+// can be the operand; W was split when it was packed.  Reading W as planes
+// (rather than a real expansion of the complex matrix) halves its LDS and L2
+// traffic.  SPLIT: the products of each pair of stages are summed apart and
+// then added to the running sums.
+
+__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
+
+__device__ __forceinline__ f16x8 neg(const f16x8 x) {
+  return __builtin_bit_cast(f16x8, __builtin_bit_cast(u32x4, x) ^ 0x80008000u);
+}
+
+// Two FP32 values to halves in one packed conversion.  The register is hidden
+// from the compiler, which otherwise repeats the conversion element by element
+// where the halves are used again.
+__device__ __forceinline__ f16x2 round2(float a, float b) {
+  unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, f16x2));
+  asm("" : "+v"(u));
+  return __builtin_bit_cast(f16x2, u);
+}
+
+// Raises *slot to the exponent + 4096 of the wave's largest m (m >= 0 in every
+// lane).  Most waves find it there already and leave the atomic out.
+__device__ __forceinline__ void raise_exponent(float m, uint32_t* slot) {
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  if ((threadIdx.x & 63) == 0 && m > 0) {
+    int e;
+    frexpf(m, &e);  // m = f 2^e, f in [0.5, 1)
+    const uint32_t x = (uint32_t)(e + 4096);
+    if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < x) atomicMax(slot, x);
+  }
+}
+
+#define PSIM_LDS(p) ((__attribute__((address_space(3))) void*)(p))
+
+template <int WVM, int WVN, int MBLK, int NBLK, bool SPLIT>
+__device__ __forceinline__ void site_f16_body(const F16Args& p, const long long t) {
+  constexpr int NW = WVM * WVN;
+  constexpr int BM = WVM * MBLK * 32, BN = WVN * NBLK * 32;
+  constexpr int A_INS = BM / 8 / NW, B_INS = BN / 8 / NW;   // wave-wide 1 KB copies (8 rows of 128 bytes)
+  static_assert(A_INS >= 1 && B_INS >= 1 && A_INS * NW * 8 == BM && B_INS * NW * 8 == BN, "tile");
+  __shared__ __attribute__((aligned(1024))) float sA0[BM * 32];
+  __shared__ __attribute__((aligned(1024))) float sA1[BM * 32];
+  __shared__ __attribute__((aligned(1024))) float sB0[BN * 32];
+  __shared__ __attribute__((aligned(1024))) float sB1[BN * 32];
+
+  const long long nt = t % p.NT;
+  const long long rest = t / p.NT;
+  const long long mt = rest % p.MT;
+  const long long z = rest / p.MT;
+  const long long node = z / p.Bz, vb = z % p.Bz;
+  const long long ablk = p.a_index ? (long long)p.a_index[node] : node;
+  const float* __restrict__ A = p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
+  const int tauv = p.tau ? (int)p.tau[node * p.tau_stride] : 0;
+  const char* __restrict__ W = (const char*)(tauv ? p.W1 : p.W0);
+  float* __restrict__ C = p.C + 2 * (node * p.sC_node + vb * p.sC_v);
+  const long long m0 = mt * BM;
+  const uint32_t am = p.amax_in ? p.amax_in[node] : 0;
+  const int e_a = p.a_exp + (am ? (int)am - 4096 : 0);
+  const int sa = min(kTop - e_a, 127);
+  const float scale = ldexpf(1.0f, sa);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wid = tid >> 6;
+  const int wr = wid / WVN, wc = wid % WVN;
+  const long long sK1 = p.M * p.K2;
+
+  // A stage is 16 complex k: rows of 128 bytes of A and of the packed W
+  // (hi / lo halves of Re and Im), 8 chunks of 16 bytes.  Copy `it` of a
+  // wave fills tile rows (it * NW + wid) * 8 + lane / 8, physical chunk
+  // lane % 8, from logical chunk (lane % 8) ^ swz(row).
+  unsigned aoff[A_INS], boff[B_INS];
+  const int K2 = (int)p.K2;
+#pragma unroll
+  for (int it = 0; it < A_INS; ++it) {
+    const int row = (it * NW + wid) * 8 + (lane >> 3);
+    const int kc = 2 * ((lane & 7) ^ swz(row));   // complex k of the chunk inside the stage
+    const long long r = min((long long)row, p.M - 1 - m0);
+    const int q = K2 < 16 ? kc / K2 : 0;
+    aoff[it] = (unsigned)((q * sK1 + r * K2 + (kc - q * K2)) * 8);
+  }
+#pragma unroll
+  for (int it = 0; it < B_INS; ++it) {
+    const int row = (it * NW + wid) * 8 + (lane >> 3);
+    const long long r = min((long long)row, p.N - 1 - nt * BN);
+    boff[it] = (unsigned)(r * p.ldw) + (unsigned)((lane & 7) ^ swz(row)) * 16u;
+  }
+  const char* abase = (const char*)(A + 2 * m0 * p.K2);
+  const char* bbase = W + nt * BN * p.ldw;
+  const long long a_k1 = sK1 * 8 * (K2 < 16 ? 16 / K2 : 1);  // bytes from one k1 step of the stages to the next
+  int fk2 = 0;
+  auto issue = [&](float* da, float* db) {
+#pragma unroll
+    for (int it = 0; it < A_INS; ++it)
+      __builtin_amdgcn_global_load_lds((const void*)(abase + aoff[it]), PSIM_LDS(da + (it * NW + wid) * 256), 16, 0, 0);
+#pragma unroll
+    for (int it = 0; it < B_INS; ++it)
+      __builtin_amdgcn_global_load_lds((const void*)(bbase + boff[it]), PSIM_LDS(db + (it * NW + wid) * 256), 16, 0, 0);
+    bbase += 128;
+    fk2 += 16;
+    if (fk2 >= K2) {
+      abase += a_k1 - (long long)(fk2 - 16) * 8;
+      fk2 = 0;
+    } else {
+      abase += 128;
+    }
+  };
+
+  f32x16 acc[MBLK][NBLK][2];
+#pragma unroll
+  for (int bi = 0; bi < MBLK; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[bi][bj][q][r] = 0;
+  f32x16 part[SPLIT ? MBLK : 1][SPLIT ? NBLK : 1][2];
+
+  const int frow = lane & 31, h = lane >> 5;   // lane half h supplies k 8h .. 8h+7 of the stage
+  auto compute = [&](const float* as, const float* bs, const bool open, const bool close) {
+    if (SPLIT && open) {
+#pragma unroll
+      for (int bi = 0; bi < MBLK; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[bi][bj][q][r] = 0;
+    }
+    auto& dst = [&]() -> auto& {
+      if constexpr (SPLIT) return part;
+      else return acc;
+    }();
+    f16x8 w[NBLK][4];  // Re hi, Re lo, Im hi, Im lo
+#pragma unroll
+    for (int bj = 0; bj < NBLK; ++bj) {
+      const int r = (wc * NBLK + bj) * 32 + frow;
+      const int sw = swz(r);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[bj][q] = *(const f16x8*)(bs + r * 32 + (((2 * q + h) ^ sw) << 2));
+    }
+#pragma unroll
+    for (int bi = 0; bi < MBLK; ++bi) {
+      const int r = (wr * MBLK + bi) * 32 + frow;
+      const int sw = swz(r);
+      f16x8 rh, rl, ih, il;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {  // two complex k per chunk
+        const f32x4 x = *(const f32x4*)(as + r * 32 + (((4 * h + c) ^ sw) << 2));
+        const f16x2 hr = round2(ldexpf(x[0], sa), ldexpf(x[2], sa));
+        const f16x2 hi = round2(ldexpf(x[1], sa), ldexpf(x[3], sa));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          rh[2 * c + e] = hr[e];
+          ih[2 * c + e] = hi[e];
+          rl[2 * c + e] = (_Float16)fmaf(x[2 * e], scale, -(float)hr[e]);
+          il[2 * c + e] = (_Float16)fmaf(x[2 * e + 1], scale, -(float)hi[e]);
+        }
+      }
+      const f16x8 nh = neg(ih), nl = neg(il);
+#define PSIM_MM(a, b, c) c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0)
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        PSIM_MM(rl, w[bj][0], dst[bi][bj][0]);
+        PSIM_MM(rl, w[bj][2], dst[bi][bj][1]);
+      }
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        PSIM_MM(nl, w[bj][2], dst[bi][bj][0]);
+        PSIM_MM(il, w[bj][0], dst[bi][bj][1]);
+      }
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        PSIM_MM(rh, w[bj][1], dst[bi][bj][0]);
+        PSIM_MM(rh, w[bj][3], dst[bi][bj][1]);
+      }
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        PSIM_MM(nh, w[bj][3], dst[bi][bj][0]);
+        PSIM_MM(ih, w[bj][1], dst[bi][bj][1]);
+      }
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        PSIM_MM(rh, w[bj][0], dst[bi][bj][0]);
+        PSIM_MM(rh, w[bj][2], dst[bi][bj][1]);
+      }
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        PSIM_MM(nh, w[bj][2], dst[bi][bj][0]);
+        PSIM_MM(ih, w[bj][0], dst[bi][bj][1]);
+      }
+#undef PSIM_MM
+    }
+    if (SPLIT && close) {
+#pragma unroll
+      for (int bi = 0; bi < MBLK; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) acc[bi][bj][q] += part[bi][bj][q];
+    }
+  };
+  constexpr unsigned kWaitVm0 = 0x3f70;  // vmcnt(0), other counters unconstrained
+
+  issue(sA0, sB0);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __syncthreads();
+  const int nst = p.nst;
+  int s = 0;
+  for (; s + 1 < nst; s += 2) {
+    issue(sA1, sB1);
+    compute(sA0, sB0, true, false);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+    if (s + 2 < nst) issue(sA0, sB0);
+    compute(sA1, sB1, false, true);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+  }
+  if (s < nst) compute(sA0, sB0, true, true);
+
+  const int sc = p.w_exp - sa - kTopW;
+  float mx = 0;
+#pragma unroll
+  for (int bi = 0; bi < MBLK; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const long long row = m0 + (wr * MBLK + bi) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+        const long long col = nt * BN + (wc * NBLK + bj) * 32 + frow;
+        if (row < p.M && col < p.N) {
+          const f32x2 v = {ldexpf(acc[bi][bj][0][r], sc), ldexpf(acc[bi][bj][1][r], sc)};
+          mx = fmaxf(mx, fmaxf(fabsf(v[0]), fabsf(v[1])));
+          *(f32x2*)(C + 2 * (row * p.N + col)) = v;
+        }
+      }
+  if (p.amax_out) raise_exponent(mx, p.amax_out + node);
+}
+
+template <int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
+__global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16(F16Args p) {
+  // XCD-aware order: workgroup b runs on XCD b mod 8; each XCD gets a contiguous range of tiles
+  const long long per_xcd = (p.T + 7) / 8;
+  const long long t = (long long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t >= p.T) return;
+  site_f16_body<WVM, WVN, MBLK, NBLK, SPLIT>(p, t);
+}
+
+// Several contractions in one grid: problem i owns tiles [start[i],
+// start[i+1]), its arguments lie in device memory.
+constexpr int kMaxProbs = 32;
+struct F16Group {
+  const F16Args* probs[kMaxProbs];
+  long long start[kMaxProbs + 1];
+  int nprob;
+};
+
+template <int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
+__global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16_group(F16Group ga) {
+  const long long total = ga.start[ga.nprob];
+  const long long per_xcd = (total + 7) / 8;
+  const long long g = (long long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (g >= total) return;
+  int lo = 0, hi = ga.nprob - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (ga.start[mid] <= g) lo = mid; else hi = mid - 1;
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  F16Args p;
+  const int* src = (const int*)ga.probs[lo];
+  int* dst = (int*)&p;
+#pragma unroll
+  for (int w = 0; w < (int)(sizeof(F16Args) / 4); ++w) dst[w] = __builtin_amdgcn_readfirstlane(src[w]);
+  site_f16_body<WVM, WVN, MBLK, NBLK, SPLIT>(p, g - ga.start[lo]);
+}
+
+// Packed FP32 rows (Re, Im interleaved along k, groups of 16 complex k = 128
+// bytes) to Re hi, Re lo, Im hi, Im lo halves of the same 16 k, scaled by
+// 2^kTopW.  One thread per group, so src and dst may be the same.
+__global__ void pack_w_f16(const float* src, float* dst, long long groups) {
+  for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < groups;
+       g += (long long)gridDim.x * blockDim.x) {
+    f32x4 x[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) x[c] = *(const f32x4*)(src + 32 * g + 4 * c);
+    f16x8 o[8];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float y = ldexpf(x[k >> 1][2 * (k & 1) + q], kTopW);
+        const _Float16 hi = (_Float16)y;
+        o[4 * q + (k >> 3)][k & 7] = hi;
+        o[4 * q + 2 + (k >> 3)][k & 7] = (_Float16)(y - (float)hi);
+      }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) *(f16x8*)(dst + 32 * g + 4 * c) = o[c];
+  }
+}
+
+// Exponent + 4096 of the largest component of each node's tensor (out zeroed before).
+__global__ __launch_bounds__(256) void exponents_f16(const float* __restrict__ A, long long len, long long stride,
+                                                     uint32_t* out) {
+  const float* a = A + (long long)blockIdx.y * stride;
+  float m = 0;
+  // infinities and NaN stay out: they must not set the scale of the finite rows
+  auto take = [&](float v) {
+    v = fabsf(v);
+    if (v < __builtin_inff()) m = fmaxf(m, v);
+  };
+  for (long long x = (long long)blockIdx.x * 256 + threadIdx.x; 4 * x + 3 < len; x += (long long)gridDim.x * 256) {
+    const f32x4 v = *(const f32x4*)(a + 4 * x);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) take(v[e]);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    for (long long x = len / 4 * 4; x < len; ++x) take(a[x]);
+  raise_exponent(m, out + blockIdx.y);
+}
+
+}  // namespace
+
+void launch_pack_w_f16(const void* src, void* dst, int64_t groups, void* stream) {
+  const long long b = std::max<long long>(1, std::min<long long>((groups + 255) / 256, 1 << 16));
+  hipLaunchKernelGGL(pack_w_f16, dim3((unsigned)b), dim3(256), 0, (hipStream_t)stream, (const float*)src, (float*)dst,
+                     (long long)groups);
+  hip_check(hipGetLastError(), "pack_w_f16 launch");
+}
+
+void launch_exponents_f16(const void* A, int64_t per_node, int64_t stride, int64_t nodes, uint32_t* out, void* stream) {
+  launch_zero_u32(out, nodes, stream);
+  const long long gx = std::max<long long>(1, std::min<long long>((2 * per_node + 4095) / 4096, 2048));
+  for (int64_t n0 = 0; n0 < nodes; n0 += 65535) {
+    const int64_t n = std::min<int64_t>(65535, nodes - n0);
+    hipLaunchKernelGGL(exponents_f16, dim3((unsigned)gx, (unsigned)n), dim3(256), 0, (hipStream_t)stream,
+                       (const float*)A + 2 * n0 * stride, (long long)(2 * per_node), (long long)(2 * stride), out + n0);
+  }
+  hip_check(hipGetLastError(), "exponents_f16 launch");
+}
+
+// Stages of 16 complex k: inside one k1 block (K2 a multiple of 16) or whole
+// k1 blocks (K2 = 2, 4, 8), read as 16-byte chunks (K2 even).  The copies'
+// offsets from a stage's base are 32-bit: 128 rows of A, and for a small K2
+// 16 / K2 blocks of M rows.
+bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2) {
+  return (prec == PSIM_FP32_4M || prec == PSIM_FP32_3M) && K2 % 2 == 0 && (K1 * K2) % 16 == 0 &&
+         (K2 % 16 == 0 || 16 % K2 == 0) && (K2 < 16 ? M < (1 << 24) : K2 < (1 << 21)) && K1 * K2 < (1 << 21);
+}
+
+// Tiles: every form has the same products in the same order for each output.
+//   0: 128 x 128 complex outputs, 4 waves of 64 x 64, two workgroups per CU
+//   1: 128 x 64, 4 waves of 32 x 64, three workgroups per CU
+//   2: the same with partial sums, two workgroups per CU
+static int f16_variant(const GemmLaunch& g) {
+  if (g.split) return 2;
+  const long long big = ((g.M + 127) / 128) * ((g.N + 127) / 128) * g.nodes * g.Bz;
+  return g.N % 128 == 0 && big >= 1024 ? 0 : 1;
+}
+
+static F16Args f16_args(const GemmLaunch& g, int variant) {
+  if (g.M < 1 || g.K1 < 1 || g.K2 < 1 || g.N < 1 || g.nodes < 1 || g.Bz < 1)
+    fail(PSIM_EINVAL, "site gemm: non-positive size");
+  if (!f16_site(g.prec, g.M, g.K1, g.K2) || g.trans_out || g.nb || g.beta || (uintptr_t)g.A % 16 || g.sA_node % 2 ||
+      g.sA_v % 2 || g.ldw >= (1 << 23))
+    fail(PSIM_EINTERNAL, "site gemm: shape or alignment the half-precision kernels do not take");
+  F16Args a{};
+  a.A = (const float*)g.A;
+  a.C = (float*)g.C;
+  a.W0 = (const float*)g.W0;
+  a.W1 = (const float*)(g.W1 ? g.W1 : g.W0);
+  a.a_index = g.a_index;
+  a.tau = g.tau;
+  a.tau_stride = g.tau_stride;
+  a.amax_in = g.amax_in;
+  a.amax_out = g.amax_out;
+  a.M = g.M;
+  a.K1 = g.K1;
+  a.K2 = g.K2;
+  a.N = g.N;
+  a.ldw = g.ldw * 4;
+  a.sA_node = g.sA_node;
+  a.sA_v = g.sA_v;
+  a.sC_node = g.sC_node;
+  a.sC_v = g.sC_v;
+  a.Bz = g.Bz;
+  a.nst = (int)(g.K1 * g.K2 / 16);
+  a.a_exp = g.a_exp;
+  a.w_exp = g.w_exp;
+  const int bn = variant == 0 ? 128 : 64;
+  a.MT = (a.M + 127) / 128;
+  a.NT = (a.N + bn - 1) / bn;
+  a.T = a.MT * a.NT * g.nodes * g.Bz;
+  return a;
+}
+
+void launch_site_f16(const GemmLaunch& g, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  const int variant = f16_variant(g);
+  const F16Args a = f16_args(g, variant);
+  const long long blocks = (a.T + 7) / 8 * 8;
+  if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
+  const dim3 grid((unsigned)blocks), wg(256);
+  switch (variant) {
+    case 0: hipLaunchKernelGGL((site_f16<2, 2, 2, 2, false, 2>), grid, wg, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((site_f16<4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
+    default: hipLaunchKernelGGL((site_f16<4, 1, 1, 2, true, 2>), grid, wg, 0, st, a); break;
+  }
+  hip_check(hipGetLastError(), "site_f16 launch");
+}
+
+int f16_descriptor_bytes() { return (int)sizeof(F16Args); }
+
+int group_variant_f16(const GemmLaunch& g, void* out, long long* tiles) {
+  const int variant = f16_variant(g);
+  const F16Args a = f16_args(g, variant);
+  std::memcpy(out, &a, sizeof(a));
+  *tiles = a.T;
+  return variant;
+}
+
+void launch_group_f16(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  if (nprob < 1 || nprob > kMaxProbs || variant < 0 || variant > 2) fail(PSIM_EINTERNAL, "bad f16 group");
+  F16Group ga{};
+  for (int i = 0; i < nprob; ++i) {
+    ga.probs[i] = (const F16Args*)d_probs[i];
+    ga.start[i] = start[i];
+  }
+  ga.start[nprob] = start[nprob];
+  ga.nprob = nprob;
+  if (start[nprob] < 1) return;
+  const long long blocks = (start[nprob] + 7) / 8 * 8;
+  if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
+  const dim3 grid((unsigned)blocks), wg(256);
+  switch (variant) {
+    case 0: hipLaunchKernelGGL((site_f16_group<2, 2, 2, 2, false, 2>), grid, wg, 0, st, ga); break;
+    case 1: hipLaunchKernelGGL((site_f16_group<4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
+    default: hipLaunchKernelGGL((site_f16_group<4, 1, 1, 2, true, 2>), grid, wg, 0, st, ga); break;
+  }
+  hip_check(hipGetLastError(), "grouped site_f16 launch");
+}
+
+}  // namespace psim

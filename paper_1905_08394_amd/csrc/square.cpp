@@ -86,10 +86,12 @@ struct SquarePlan {
   int64_t tmax = 1;            // largest running tensor (complex elements)
   int64_t qmax = 1;            // largest quadrant / joined tensor
   int64_t prow[2] = {0, 0}, pld[2] = {0, 0};  // packed operands of the two joins
-  // join j reads its quadrant tensor itself as the W operand (ld = 2K, no
-  // packing): FP32 3M with every tile interior (the direct-to-LDS kernel)
+  // FP32, K a multiple of 16: join j runs on the half-precision units and
+  // reads its quadrant tensor, split into halves in place, as the W operand
+  // (ld = 2K, no packed copy)
   bool direct[2] = {false, false};
-  uint64_t off_w1 = 0, off_w2 = 0, off_a = 0, off_b = 0, off_c = 0, off_p = 0, off_small = 0, off_y = 0;
+  int64_t sites_max = 1;       // most sites of a quadrant (amax slots of its running tensor)
+  uint64_t off_w1 = 0, off_w2 = 0, off_a = 0, off_b = 0, off_c = 0, off_p = 0, off_small = 0, off_amax = 0, off_y = 0;
   int ycap = 1;                // Y tensors held at once (lower-left patterns joined per pass)
   // batched form (chunk > 0): the bitstrings of a chunk have every quadrant
   // pattern contracted in one set of launches (the pattern is the node
@@ -181,6 +183,7 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
       }
     sq->qmax = std::max(sq->qmax, Q.dv * Q.dh);
     sq->cmac_quads += Q.cmac;
+    sq->sites_max = std::max(sq->sites_max, (int64_t)Q.s.size());
   }
   const int64_t vUL = sq->q[0].dv, vUR = sq->q[1].dv, hU = sq->q[0].dh, hL = sq->q[2].dh;
   if (sq->q[1].dh != hU || sq->q[2].dv != vUL || sq->q[3].dv != vUR || sq->q[3].dh != hL)
@@ -192,7 +195,7 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
   // join 1 reads Q_UL as W (N = vUL, K = hU), join 2 reads Q_LL (N = hL, K = vUL); M = vUR for both
   const int64_t jn[2] = {vUL, hL}, jk[2] = {hU, vUL};
   for (int j = 0; j < 2; ++j) {
-    sq->direct[j] = prec == PSIM_FP32_3M && vUR % 128 == 0 && jn[j] % 128 == 0 && jk[j] % 32 == 0;
+    sq->direct[j] = f16_site(prec, vUR, 1, jk[j]);
     sq->prow[j] = sq->direct[j] ? 0 : packed_rows(prec, jn[j]);
     sq->pld[j] = sq->direct[j] ? 2 * jk[j] : packed_ld(prec, jk[j]);
   }
@@ -211,6 +214,8 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
   off += al((uint64_t)std::max(sq->prow[0] * sq->pld[0], sq->prow[1] * sq->pld[1]) * rb);
   sq->off_small = off;
   off += al(16 + (uint64_t)cdot_blocks() * 16 + (uint64_t)kSqExpSlots * 4 + (uint64_t)kSqDotSlots * 16);
+  sq->off_amax = off;  // per node (at most kSqChunk): the sites of the running quadrant, then T
+  off += al((uint64_t)(sq->sites_max + 1) * kSqChunk * 4);
   // more Y tensors (one per lower-left pattern of a pass) from what the
   // budget leaves, so each lower-right quadrant is contracted once per pass
   sq->off_y = off;
@@ -285,11 +290,14 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
         dm.exp2 = exponent_of_max_sq(W);
         const double sc = std::ldexp(1.0, -dm.exp2);
         for (cd& x : W) x *= sc;
-        pack_site_matrix(prec, W.data(), K, N, buf, dm.ld);
+        const Shape sh = site_shape(Q, (int)(&st - &Q.s[0]) / Q.nc, (int)(&st - &Q.s[0]) % Q.nc);
+        dm.f16 = f16_site(prec, sh.M, sh.K1, sh.K2);
+        pack_site_matrix(dm.f16 ? (int)PSIM_FP32_3M : prec, W.data(), K, N, buf, dm.ld);
         pl->weights_bytes += buf.size();
         if (!pl->host_only) {
           hip_check(hipMalloc(&dm.ptr, buf.size()), "hipMalloc(site matrix)");
           hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
+          if (dm.f16) launch_pack_w_f16(dm.ptr, dm.ptr, (int64_t)(buf.size() / 128), nullptr);
         }
       }
     }
@@ -310,6 +318,7 @@ struct SqRun {
   int32_t* d_zero;
   uint32_t* d_mx;
   double* d_part;
+  uint32_t* d_amax;      // sites_max * kSqChunk words for a quadrant's sites, kSqChunk for T
   int32_t* d_exps;       // kSqExpSlots exponent slots
   double* d_dots;        // kSqDotSlots (re, im) inner products
   double* out = nullptr;
@@ -446,6 +455,40 @@ struct SqRun {
     return dot_next++;
   }
 
+  // Largest components along a quadrant row, as the f16 sites need them: the
+  // row starts from a tensor below 1 (the scalar 1 in row 0), other sites let
+  // the bound grow, f16 sites measure their output into a slot per node.
+  struct Bound {
+    int exp = 0;
+    const uint32_t* max = nullptr;
+  };
+  void clear_amax(const SqQuad& Q) {
+    for (const SqSite& s : Q.s)
+      if (s.w[0].f16) {
+        run(3, 0, 0, [&] { launch_zero_u32(d_amax, sq->sites_max * kSqChunk, st); });
+        return;
+      }
+  }
+  void bound_site(GemmLaunch& g, const DevMatrix& w, size_t site, Bound& b) {
+    if (!w.f16) {
+      b.exp += growth_exp(g.K1 * g.K2);
+      return;
+    }
+    g.f16 = 1;
+    g.a_exp = b.exp;
+    g.amax_in = b.max;
+    g.amax_out = d_amax + site * kSqChunk;
+    b = Bound{0, g.amax_out};
+  }
+  uint32_t* t_amax(int t) const { return d_amax + sq->sites_max * kSqChunk + t; }
+  void clear_t_amax() {
+    if (sq->direct[1]) run(3, 0, 0, [&] { launch_zero_u32(t_amax(0), kSqChunk, st); });
+  }
+  // a quadrant tensor (N x K) that a join reads as its W operand
+  void split_w(void* Q, int64_t N, int64_t K, int64_t nodes) {
+    run(2, 0, 2.0 * eb * N * K * nodes, [&] { launch_pack_w_f16(Q, Q, nodes * N * K / 16, st); });
+  }
+
   // Contract quadrant qi for bits into dst; returns its exponent.
   Exp quad(int qi, const uint8_t* bits, char* dst) {
     const SqQuad& Q = sq->q[qi];
@@ -454,7 +497,9 @@ struct SqRun {
     char* nxt = buf(sq->off_w2);
     Exp e;
     int64_t cur_elems = 1;
+    clear_amax(Q);
     for (int i = 0; i < nr; ++i) {
+      Bound bound{i == 0 ? 1 : 0, nullptr};
       for (int j = 0; j < nc; ++j) {
         const SqSite& st_ = Q.s[(size_t)i * nc + j];
         const int tau = bits[st_.qubit];
@@ -463,7 +508,6 @@ struct SqRun {
         GemmLaunch g;
         g.prec = prec;
         g.split = split;
-        g.cfg = (split && prec == PSIM_FP32_3M) ? 3 : 0;  // the 64 x 128 split tile, as for the joins
         g.A = (i == 0 && j == 0) ? pl->d_ones : (const void*)cur;
         g.C = nxt;
         g.W0 = g.W1 = w.ptr;
@@ -476,6 +520,7 @@ struct SqRun {
         g.Bz = 1;
         g.sA_node = sh.K1 * sh.M * sh.K2;
         g.sC_node = sh.M * sh.N;
+        bound_site(g, w, (size_t)i * nc + j, bound);
         run(0, (double)sh.M * sh.K1 * sh.K2 * sh.N, (double)eb * (sh.M * sh.K1 * sh.K2 + sh.M * sh.N),
             [&] { launch_site_gemm(g, st); });
         e.host += w.exp2;
@@ -511,7 +556,9 @@ struct SqRun {
     char* nxt = r1;
     std::vector<int64_t> row_slot;
     int64_t cur_elems = 1;
+    clear_amax(Q);
     for (int i = 0; i < nr; ++i) {
+      Bound bound{i == 0 ? 1 : 0, nullptr};
       for (int j = 0; j < nc; ++j) {
         const SqSite& st_ = Q.s[(size_t)i * nc + j];
         if (st_.w[0].ld != st_.w[1].ld) fail(PSIM_EINTERNAL, "site matrices of one site differ in layout");
@@ -520,7 +567,6 @@ struct SqRun {
         GemmLaunch g;
         g.prec = prec;
         g.split = split;
-        g.cfg = (split && prec == PSIM_FP32_3M) ? 3 : 0;  // the 64 x 128 split tile, as for the joins
         g.A = first ? pl->d_ones : (const void*)cur;
         g.C = nxt;
         g.W0 = st_.w[0].ptr;
@@ -536,6 +582,7 @@ struct SqRun {
         g.Bz = 1;
         g.sA_node = first ? 0 : sh.K1 * sh.M * sh.K2;  // every node reads the scalar 1 first
         g.sC_node = sh.M * sh.N;
+        bound_site(g, st_.w[0], (size_t)i * nc + j, bound);
         run(0, (double)nodes * sh.M * sh.K1 * sh.K2 * sh.N,
             (double)eb * nodes * (sh.M * sh.K1 * sh.K2 + sh.M * sh.N), [&] { launch_site_gemm(g, st); });
         std::swap(cur, nxt);
@@ -553,14 +600,20 @@ struct SqRun {
     return row_slot;
   }
 
-  static GemmLaunch join_launch(int prec, int split, const void* A, int64_t M, int64_t K, const void* P, int64_t ld,
-                                int64_t N, void* C) {
+  // Join j (0: T, 1: Y); t_max: the slot of T's largest component.
+  GemmLaunch join_launch(int j, const void* A, int64_t M, int64_t K, const void* P, int64_t ld, int64_t N, void* C,
+                         uint32_t* t_max) const {
     GemmLaunch g;
+    g.f16 = sq->direct[j];
+    if (g.f16 && j == 0 && sq->direct[1]) g.amax_out = t_max;
+    if (g.f16 && j == 1) {  // T from join 0 on the same units, or bounded by its K
+      if (sq->direct[0])
+        g.amax_in = t_max;
+      else
+        g.a_exp = growth_exp(sq->q[0].dh);
+    }
     g.prec = prec;
     g.split = split;
-    // split 3M joins: the 64 x 128 split tile (no spills, three workgroups
-    // per CU; the 128 x 128 one is taken where M is not a multiple of 64)
-    g.cfg = (split && prec == PSIM_FP32_3M) ? 3 : 0;
     g.A = A;
     g.C = C;
     g.W0 = g.W1 = P;
@@ -614,25 +667,8 @@ struct SqRun {
           [&] { launch_site_gemm(g, st); });
   }
 
-  void gemm(const void* A, int64_t M, int64_t K, const void* P, int64_t ld, int64_t N, void* C) {
-    GemmLaunch g;
-    g.prec = prec;
-    g.split = split;
-    // split 3M joins: the 64 x 128 split tile (no spills, three workgroups
-    // per CU; the 128 x 128 one is taken where M is not a multiple of 64)
-    g.cfg = (split && prec == PSIM_FP32_3M) ? 3 : 0;
-    g.A = A;
-    g.C = C;
-    g.W0 = g.W1 = P;
-    g.ldw = ld;
-    g.M = M;
-    g.K1 = 1;
-    g.K2 = K;
-    g.N = N;
-    g.nodes = 1;
-    g.Bz = 1;
-    g.sA_node = M * K;
-    g.sC_node = M * N;
+  void gemm(int j, const void* A, int64_t M, int64_t K, const void* P, int64_t ld, int64_t N, void* C) {
+    const GemmLaunch g = join_launch(j, A, M, K, P, ld, N, C, t_amax(0));
     run(1, (double)M * K * N, (double)eb * (M * K + K * N + M * N), [&] { launch_site_gemm(g, st); });
   }
   void pack(const void* Q, void* P, int64_t N, int64_t K, int64_t rows, int64_t ld, int64_t nodes = 1) {
@@ -743,8 +779,11 @@ void run_chunks(SqRun& R, const uint8_t* bits, const std::vector<size_t>& order,
     if (new_t) {
       // upper half: T per distinct (UL, UR)
       const std::vector<int64_t> sUL = quad(0), sUR = quad(1);
-      if (!sq->direct[0])
+      if (sq->direct[0])
+        R.split_w(qptr(0, 0), vUL, hU, (int64_t)rep[0].size());
+      else
         R.pack(qptr(0, 0), R.buf(sq->boff_pk[0]), vUL, hU, sq->prow[0], sq->pld[0], (int64_t)rep[0].size());
+      R.clear_t_amax();
       auto w_ul = [&](int p) -> const char* {
         return sq->direct[0] ? qptr(0, p) : R.buf(sq->boff_pk[0]) + (uint64_t)p * sq->prow[0] * sq->pld[0] * rb;
       };
@@ -761,16 +800,16 @@ void run_chunks(SqRun& R, const uint8_t* bits, const std::vector<size_t>& order,
         }
       }
       for (size_t t = 0; t < pairs.size(); ++t)
-        gl.push_back(SqRun::join_launch(
-            R.prec, R.split, qptr(1, pairs[t].second), vUR, hU,
-            w_ul(pairs[t].first), sq->pld[0], vUL,
-            Tst + (uint64_t)t * vUR * vUL * eb));
+        gl.push_back(R.join_launch(0, qptr(1, pairs[t].second), vUR, hU, w_ul(pairs[t].first), sq->pld[0], vUL,
+                                   Tst + (uint64_t)t * vUR * vUL * eb, R.t_amax((int)t)));
       R.joins(gl, R.buf(sq->boff_desc[0]), uploads);
     }
     if (new_y) {
       // lower-left: Y per distinct (pair, LL)
       const std::vector<int64_t> sLL = quad(2);
-      if (!sq->direct[1])
+      if (sq->direct[1])
+        R.split_w(qptr(2, 0), hL, vUL, (int64_t)rep[2].size());
+      else
         R.pack(qptr(2, 0), R.buf(sq->boff_pk[1]), hL, vUL, sq->prow[1], sq->pld[1], (int64_t)rep[2].size());
       auto w_ll = [&](int p) -> const char* {
         return sq->direct[1] ? qptr(2, p) : R.buf(sq->boff_pk[1]) + (uint64_t)p * sq->prow[1] * sq->pld[1] * rb;
@@ -790,10 +829,8 @@ void run_chunks(SqRun& R, const uint8_t* bits, const std::vector<size_t>& order,
       }
       gl.clear();
       for (size_t t = 0; t < tris.size(); ++t)
-        gl.push_back(SqRun::join_launch(
-            R.prec, R.split, Tst + (uint64_t)tris[t].first * vUR * vUL * eb, vUR, vUL,
-            w_ll(tris[t].second), sq->pld[1], hL,
-            Yst + (uint64_t)t * vUR * hL * eb));
+        gl.push_back(R.join_launch(1, Tst + (uint64_t)tris[t].first * vUR * vUL * eb, vUR, vUL, w_ll(tris[t].second),
+                                   sq->pld[1], hL, Yst + (uint64_t)t * vUR * hL * eb, R.t_amax(tris[t].first)));
       R.joins(gl, R.buf(sq->boff_desc[1]), uploads);
     }
     // lower-right, then one inner product per distinct (Y, LR)
@@ -835,6 +872,7 @@ void run_square(psim_plan_t* pl, const uint8_t* bits, size_t n, void* ws, void* 
   R.d_zero = (int32_t*)small;
   R.d_mx = (uint32_t*)(small + 8);
   R.d_part = (double*)(small + 16);
+  R.d_amax = (uint32_t*)R.buf(sq->off_amax);
   R.d_exps = (int32_t*)(small + 16 + (size_t)cdot_blocks() * 16);
   R.d_dots = (double*)(small + 16 + (size_t)cdot_blocks() * 16 + (size_t)kSqExpSlots * 4);
   R.out = out;
@@ -880,8 +918,12 @@ void run_square(psim_plan_t* pl, const uint8_t* bits, size_t n, void* ws, void* 
     const uint8_t* b0 = bits + order[x] * nq;
     SqRun::Exp eT = R.quad(0, b0, A);           // Q_UL [vUL][hU]
     eT += R.quad(1, b0, B);                     // Q_UR [vUR][hU]
-    if (!sq->direct[0]) R.pack(A, P, vUL, hU, sq->prow[0], sq->pld[0]);
-    R.gemm(B, vUR, hU, sq->direct[0] ? A : P, sq->pld[0], vUL, C);  // T [vUR][vUL]
+    if (sq->direct[0])
+      R.split_w(A, vUL, hU, 1);
+    else
+      R.pack(A, P, vUL, hU, sq->prow[0], sq->pld[0]);
+    R.clear_t_amax();
+    R.gemm(0, B, vUR, hU, sq->direct[0] ? A : P, sq->pld[0], vUL, C);  // T [vUR][vUL]
     size_t y = x;
     while (y < xe) {
       // one pass: up to ycap lower-left patterns, each joined into its Y
@@ -893,8 +935,11 @@ void run_square(psim_plan_t* pl, const uint8_t* bits, size_t n, void* ws, void* 
         const int k = (int)eY.size();
         SqRun::Exp e = eT;
         e += R.quad(2, bb, A);                  // Q_LL [hL][vUL]
-        if (!sq->direct[1]) R.pack(A, P, hL, vUL, sq->prow[1], sq->pld[1]);
-        R.gemm(C, vUR, vUL, sq->direct[1] ? A : P, sq->pld[1], hL, ybuf(k));  // Y [vUR][hL]
+        if (sq->direct[1])
+          R.split_w(A, hL, vUL, 1);
+        else
+          R.pack(A, P, hL, vUL, sq->prow[1], sq->pld[1]);
+        R.gemm(1, C, vUR, vUL, sq->direct[1] ? A : P, sq->pld[1], hL, ybuf(k));  // Y [vUR][hL]
         eY.push_back(e);
         size_t z = ye;
         while (z < xe && same(order[ye], order[z], 3)) slot[z++ - y] = k;
