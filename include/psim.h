@@ -303,7 +303,8 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
  * precision and shape (M, K1, K2, N, batch entries), and later plans start
  * from them.  Split-accumulation plans choose among their split kernels'
  * tiles (FP32 3M: 128 x 128 or 64 x 128; other precisions have one, and
- * nothing is timed); square-partition plans keep their single configuration.  Captured graphs of
+ * nothing is timed); square-partition plans and plans of small networks (rows that fit the
+ * LDS of a CU run whole) keep their single configuration.  Captured graphs of
  * the plan are dropped when a choice changes.
  * Errors: EINVAL for a short workspace, reps < 1 or an unwritable cache file,
  * EDEVICE. */

@@ -123,7 +123,7 @@ void tune_plan(psim_plan_t* pl, void* ws, size_t ws_bytes, void* stream, int rep
   if (!ws || ws_bytes < pl->ws_total) fail(PSIM_EINVAL, "workspace is NULL or smaller than the plan needs");
   if (reps < 1) fail(PSIM_EINVAL, "reps must be at least 1");
   if (best_ms) *best_ms = 0;
-  if (pl->sq) return;
+  if (pl->sq || pl->small) return;
   const bool split = (pl->opts.flags & PSIM_PLAN_SPLIT_ACC) != 0;
   std::vector<int> cands;
   for (int cfg = 0; cfg < config_count(pl->opts.prec); ++cfg)
@@ -263,9 +263,12 @@ std::vector<std::vector<size_t>> split_batches(const psim_plan_t* pl, const uint
   return out;
 }
 
-// One device operation of the row sweep: a site contraction or a row rescale.
+// One device operation of the row sweep: a site contraction, a row rescale, or
+// a whole row (or its sum over v) of a small network.
 struct Op {
   bool rescale = false;
+  int small = -1;  // 0: sr itself, 1: its sum over v
+  SmallRow sr;
   int cls = 0;  // 0 first site, 1 interior site, 2 last site, 3 rescale
   double cmac = 0;
   double bytes = 0;  // algorithmic device-memory traffic
@@ -327,6 +330,49 @@ void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
     const int c = lev.vchunk;
     const bool wc = w_cut(lev);
     const int cw = wc ? lev.wchunk : 1;
+    if (pl->small) {
+      for (int64_t g0 = 0; g0 < nodes; g0 += lev.group) {
+        Op op;
+        SmallRow& r = op.sr;
+        r = SmallRow{};
+        r.F_in = Fprev;
+        r.F_out = Fcur + (uint64_t)g0 * lev.F_elems * eb;
+        r.part = W.G[0];
+        r.parent = W.parent[i] + g0;
+        r.tau = W.tau[i] + g0 * L;
+        r.exp_prev = W.exp[(i + 1) % 2];
+        r.exp_cur = W.exp[i % 2] + g0;
+        for (int j = 0; j < L; ++j) {
+          const CSite& s = pl->cs[(size_t)i * L + j];
+          r.site[j] = SmallSite{s.du, s.dl, s.dr, s.dd};
+          for (int tau = 0; tau < 2; ++tau) r.W[j][tau] = pl->w[((size_t)i * L + j) * 2 + tau].ptr;
+          const Step& st = pl->steps[(size_t)i * L + j];
+          op.cmac += (double)st.M * st.K2 * st.N * (st.kind == 2 ? 1 : st.K1);
+        }
+        r.L = L;
+        r.Dv = lev.Dv;
+        r.nodes = (int)std::min<int64_t>(lev.group, nodes - g0);
+        r.gmax = (int)lev.gmax;
+        r.Fprev = (int)Fprev_elems;
+        r.F = (int)lev.F_elems;
+        r.vc = lev.vc;
+        const int parts = lev.Dv / lev.vc;
+        op.nodes = r.nodes;
+        op.cmac *= (double)r.nodes * lev.Dv;
+        op.bytes = (double)eb * r.nodes * (Fprev_elems + (double)lev.F_elems * parts);
+        op.cls = 1;
+        op.row = i;
+        op.small = 0;
+        P.ops.push_back(op);
+        if (parts == 1) continue;
+        op.small = 1;
+        op.cls = 3;
+        op.cmac = 0;
+        op.bytes = (double)eb * r.nodes * lev.F_elems * (parts + 1);
+        P.ops.push_back(op);
+      }
+      continue;
+    }
     const int64_t rows_per_col = (prec == PSIM_FP32_3M) ? 1 : 2;  // packed rows per complex column (first site)
     for (int64_t g0 = 0; g0 < nodes; g0 += lev.group) {
       const int64_t gn = std::min<int64_t>(lev.group, nodes - g0);
@@ -491,8 +537,14 @@ void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
   if ((int64_t)P.ops.size() > pl->max_ops) fail(PSIM_EINTERNAL, "more operations than planned");
 }
 
+// the accumulation form of a small plan's rows: the plan's, or the other one in
+// the companion sweep of an error estimate
+int small_split(const psim_plan_t* pl) { return ((pl->opts.flags & PSIM_PLAN_SPLIT_ACC) ? 1 : 0) ^ pl->companion; }
+
 void run_op(const psim_plan_t* pl, const Op& op, hipStream_t st) {
-  if (op.rescale)
+  if (op.small >= 0)
+    launch_small(op.sr, op.small, pl->opts.prec, small_split(pl), st);
+  else if (op.rescale)
     launch_rowscale(pl->opts.prec, op.F, op.F_elems, op.nodes, op.parent, const_cast<int32_t*>(op.e_in), op.e_out,
                     op.mx, st);
   else
@@ -599,7 +651,7 @@ void run_one(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
         }
         run_op(pl, op, lst);
         if (profile) hip_check(hipEventRecord(timed.back().b, lst), "hipEventRecord");
-        if (log_rows && op.rescale) {  // progress for long runs: wait for the row, then report it
+        if (log_rows && (op.rescale || (op.small >= 0 && op.small == (op.sr.vc < op.sr.Dv)))) {  // progress for long runs: wait for the row, then report it
           hip_check(hipStreamSynchronize(lst), "hipStreamSynchronize");
           std::fprintf(stderr, "psim: row %d/%d done (%lld nodes) at %.2f s\n", op.row + 1, pl->R,
                        (long long)op.nodes,
@@ -697,6 +749,8 @@ void run_amplitudes(psim_plan_t* pl, const uint8_t* bits, size_t n, void* ws, si
 // in their own order on the one stream, so each plan computes exactly what
 // psim_amplitudes computes for it.
 void free_group(psim_group_s* G);
+
+constexpr int kSmallVariant = 64;  // merged launches of small plans' rows, beyond group_variant's ids
 
 psim_group_s* make_group(psim_plan_t* const* plans, int np) {
   if (!plans || np < 1) fail(PSIM_EINVAL, "plans is NULL or empty");
@@ -811,7 +865,11 @@ void run_group(psim_group_s* G, const uint8_t* const* bits, const size_t* n, voi
       variant[q].assign(ops.size(), -1);
       tiles[q].assign(ops.size(), 0);
       for (size_t k = 0; k < ops.size(); ++k)
-        if (!ops[k].rescale) variant[q][k] = group_variant(ops[k].g, hbuf + G->desc_off[p] + k * kb, &tiles[q][k]);
+        if (ops[k].small >= 0) {  // merged with those of the same storage, accumulation and kind
+          std::memcpy(hbuf + G->desc_off[p] + k * kb, &ops[k].sr, sizeof(SmallRow));
+          variant[q][k] = kSmallVariant + 4 * (P[q].pl->elem_bytes == 16) + 2 * small_split(P[q].pl) + ops[k].small;
+        } else if (!ops[k].rescale)
+          variant[q][k] = group_variant(ops[k].g, hbuf + G->desc_off[p] + k * kb, &tiles[q][k]);
       const psim_plan_t* pl = P[q].pl;
       const int64_t leaves = (int64_t)P[q].t.parent[pl->R - 1].size();
       hseg[2 * q] = CopySeg{P[q].W.F[(pl->R - 1) % 2], dbuf + G->res_off[p], leaves * pl->elem_bytes};
@@ -845,6 +903,19 @@ void run_group(psim_group_s* G, const uint8_t* const* bits, const size_t* n, voi
           const auto& lst = kv.second;
           if (lst.size() == 1) {  // nothing to merge with
             run_op(P[lst[0].first].pl, P[lst[0].first].ops[lst[0].second], ls);
+            continue;
+          }
+          if (kv.first >= kSmallVariant) {
+            std::vector<const SmallRow*> hp;
+            std::vector<const void*> dp;
+            for (const auto& x : lst) {
+              hp.push_back(&P[x.first].ops[x.second].sr);
+              dp.push_back(dbuf + G->desc_off[who[x.first]] + x.second * kb);
+            }
+            const int v = kv.first - kSmallVariant;
+            launch_small_group(hp.data(), dp.data(), (int)hp.size(), v & 1, v & 4 ? PSIM_FP64 : PSIM_FP32_4M,
+                               (v >> 1) & 1, ls);
+            merged += 1;
             continue;
           }
           for (size_t a = 0; a < lst.size(); a += maxg) {

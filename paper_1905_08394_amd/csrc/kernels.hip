@@ -1494,7 +1494,7 @@ void launch_group(int variant, const void* const* d_probs, const long long* star
   hip_check(hipGetLastError(), "grouped site_gemm launch");
 }
 
-int kargs_bytes() { return std::max((int)sizeof(KArgs), f16_descriptor_bytes()); }
+int kargs_bytes() { return std::max({(int)sizeof(KArgs), f16_descriptor_bytes(), small_descriptor_bytes()}); }
 int max_group() { return kMaxGroup; }
 
 // FP32 launch arguments with 128 x 128 tiles over Z batch entries

@@ -174,6 +174,40 @@ int exponent_of_max(const std::vector<cd>& W) {
 
 }  // namespace psim
 
+namespace psim {
+namespace {
+
+// Whether the plan's rows run whole in LDS, and how many v values one
+// workgroup takes: all of them where they leave room for two workgroups on a
+// CU, else one (a row per node instead of per (node, v) saves the sum over v:
+// 3x3 (1+32+1) 64 bitstrings 238 against 277 us, 5x5 (1+16+1) 2048 bitstrings
+// 1.16 against 1.48 ms).  Against a launch per site it is the faster form at
+// every batch size in FP32 (4x5 (1+24+1): 16 bitstrings 371 -> 233 us, 4096 6.9
+// -> 5.8 ms; 6x6 (1+16+1): 16 522 -> 266 us, 4096 14.9 -> 6.6 ms).  In FP64 a
+// spread row loses what it gains once the batch fills the chip (5x5 (1+16+1):
+// 64 bitstrings 277 -> 178 us, 1024 1070 -> 1050 us, 4096 3.58 -> 3.70 ms), so
+// those plans are bounded by their work.  The FP64 buffers hold half as many
+// elements.  BF16x3 plans keep their own products.
+bool small_network(psim_plan_t& pl) {
+  const int prec = pl.opts.prec, R = pl.R, L = pl.L;
+  if (prec == PSIM_BF16X3 || L < 2 || L > kSmallL) return false;
+  const int64_t most = kSmallBytes / pl.elem_bytes;
+  bool spread = false;
+  for (int i = 0; i < R; ++i) {
+    Level& lev = pl.levels[i];
+    const int64_t Fprev = i ? pl.levels[i - 1].F_elems : 1;
+    const int64_t per = std::max(lev.Gmax, Fprev / lev.Dv);
+    if (std::max({per, lev.F_elems, Fprev}) > most || lev.F_elems > 2 * lev.Gmax) return false;
+    lev.vc = lev.Dv * per <= most / 2 ? lev.Dv : 1;
+    lev.gmax = std::max(lev.vc * per, lev.F_elems);
+    spread = spread || lev.vc < lev.Dv;
+  }
+  return !(spread && prec == PSIM_FP64 && pl.cmac * pl.opts.max_batch > 1e9);
+}
+
+}  // namespace
+}  // namespace psim
+
 using namespace psim;
 
 psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
@@ -286,6 +320,11 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
     pl->cmac = cmac;
     pl->peak_elems = peak;
 
+    // ---------------------------------------------------------- small networks
+    // Whole rows per launch (small.hip) where every per-v tensor of the
+    // network fits an LDS buffer.
+    pl->small = small_network(*pl);
+
     // ---------------------------------------------------------- memory plan
     // Workspace = tables + two boundary buffers (even / odd levels) + two
     // intermediate buffers (ping-pong inside a row).  Per level i the plan
@@ -310,8 +349,13 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
       Fmin[i % 2] = std::max(Fmin[i % 2], al((uint64_t)lev.F_elems * eb));
     }
     tab += 3 * al((uint64_t)nmax_all * 4);  // exponents (two levels) and row maxima
+    // a small plan needs room for the parts of every node
+    for (const Level& lev : pl->levels)
+      if (pl->small && lev.vc < lev.Dv &&
+          tab + Fmin[0] + Fmin[1] + al((uint64_t)lev.nmax * lev.Dv * lev.F_elems * eb) > budget)
+        pl->small = false;
     for (Step& st : pl->steps)  // largest components of the f16 sites' outputs
-      if (st.kind == 1 && f16_site(opts.prec, st.M, st.K1, st.K2)) st.amax = pl->n_amax++;
+      if (!pl->small && st.kind == 1 && f16_site(opts.prec, st.M, st.K1, st.K2)) st.amax = pl->n_amax++;
     tab += (uint64_t)pl->n_amax * al((uint64_t)nmax_all * 4);
     pl->ws_tab = tab;
     if (tab + Fmin[0] + Fmin[1] > budget)
@@ -321,6 +365,14 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
     uint64_t G = 0;
     for (int i = 0; i < R; ++i) {
       Level& lev = pl->levels[i];
+      if (pl->small) {  // the parts of spread rows, in passes of up to 2^26 elements
+        lev.vchunk = lev.Dv;
+        lev.wchunk = lev.Dw;
+        const uint64_t one = (uint64_t)(lev.Dv / lev.vc) * lev.F_elems;
+        lev.group = (int)std::min<uint64_t>((uint64_t)lev.nmax, std::max<uint64_t>(1, (1ull << 26) / one));
+        if (lev.vc < lev.Dv) G = std::max(G, al((uint64_t)lev.group * one * eb));
+        continue;
+      }
       if (L == 1 || lev.Gmax == 0) {
         lev.vchunk = lev.Dv;
         lev.group = (int)std::min<int64_t>(lev.nmax, 1 << 16);
@@ -409,7 +461,7 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
       const int64_t groups = (lev.cap + lev.group - 1) / lev.group;
       const int64_t chunks = L == 1 ? 1 : (lev.Dv + lev.vchunk - 1) / lev.vchunk;
       const int64_t wchunks = w_cut(lev) ? lev.Dw / lev.wchunk : 1;
-      pl->max_ops += groups * chunks * wchunks * L + 1;
+      pl->max_ops += pl->small ? groups * 2 : groups * chunks * wchunks * L + 1;
     }
     pl->ws_F = Fb[0] + Fb[1];
     pl->ws_G = G;
@@ -447,6 +499,27 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
           dm.exp2 = exponent_of_max(W);
           const double sc = std::ldexp(1.0, -dm.exp2);  // exact power of two
           for (cd& x : W) x *= sc;
+          if (pl->small) {
+            dm.ld = (int64_t)c.dd * c.dr;
+            if (opts.prec == PSIM_FP64) {
+              buf.resize(W.size() * 16);
+              std::memcpy(buf.data(), W.data(), buf.size());
+            } else {
+              buf.resize(W.size() * 8);
+              float* f = reinterpret_cast<float*>(buf.data());
+              for (size_t x = 0; x < W.size(); ++x) {
+                f[2 * x] = (float)W[x].real();
+                f[2 * x + 1] = (float)W[x].imag();
+              }
+            }
+            pl->weights_bytes += buf.size();
+            if (!pl->host_only) {
+              hip_check(hipSetDevice(opts.device), "hipSetDevice");
+              hip_check(hipMalloc(&dm.ptr, buf.size()), "hipMalloc(site matrix)");
+              hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
+            }
+            continue;
+          }
           // the last site of a row always runs the 4M transposed-store kernel
           // in FP32 plans (its 256 x 64 tile suits the few output columns)
           const bool last = (j == L - 1);

@@ -79,6 +79,8 @@ struct Level {
   int group = 1;         // nodes per pass
   int64_t nmax = 1;      // most nodes (distinct prefixes) this level can have
   int64_t cap = 1;       // nodes whose boundary fits the workspace at once
+  int vc = 1;            // small plans: v values of a workgroup (a divisor of Dv: Dv or 1)
+  int64_t gmax = 1;      // small plans: most elements of a workgroup's tensors
   uint64_t F_off = 0;    // byte offset of this level's boundary buffer in the F region
 };
 
@@ -111,6 +113,7 @@ struct psim_plan_s {
   int64_t peak_elems = 0;
   uint64_t weights_bytes = 0;
   int n_amax = 0;                        // f16 sites of the plan
+  bool small = false;                    // whole rows per launch (small.hip); site matrices plain [K][N]
   uint64_t ws_F = 0, ws_G = 0, ws_tab = 0, ws_total = 0;
   bool host_only = false;
   int elem_bytes = 8;
@@ -170,6 +173,31 @@ int64_t packed_ld(int prec, int64_t K);
 int64_t packed_rows(int prec, int64_t N);
 void pack_site_matrix(int prec, const cd* W, int64_t K, int64_t N, std::vector<char>& out, int64_t& ld);
 void pack_site_matrix_bf16(const cd* W, int64_t K, int64_t N, std::vector<char>& out, int64_t& ld, int64_t& plane);
+
+// small.hip: a row of a small network for `nodes` nodes, one workgroup each (or
+// one per v value, followed by the sum over v)
+constexpr int kSmallL = 8;              // widest boundary
+constexpr int64_t kSmallBytes = 65536;  // largest tensor of a workgroup: two of them in the 160 KB of a CU
+struct SmallSite {
+  int du, dl, dr, dd;
+};
+struct SmallRow {
+  const void* F_in;         // boundaries of the level before (Fprev elements each), [v][u_0 ..]
+  void* F_out;              // this level's, F elements each, rescaled
+  void* part;               // vc < Dv: [node][Dv / vc][F], elements [d_0 ..][d_{L-1}]
+  const int32_t* parent;
+  const uint8_t* tau;       // L values per node
+  const int32_t* exp_prev;
+  int32_t* exp_cur;
+  const void* W[kSmallL][2];  // plain complex [K][N] per site and value
+  SmallSite site[kSmallL];
+  int L, Dv, vc, nodes, gmax, Fprev, F;  // vc: v values per workgroup; gmax: most elements of its tensors
+};
+int small_blocks(const SmallRow& p, int kind);
+int small_descriptor_bytes();
+void launch_small(const SmallRow& p, int kind, int prec, int split, void* stream);
+void launch_small_group(const SmallRow* const* hp, const void* const* dp, int n, int kind, int prec, int split,
+                        void* stream);
 
 // kernels.hip: launch interface (host side)
 struct GemmLaunch {
