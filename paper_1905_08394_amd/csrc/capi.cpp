@@ -206,7 +206,7 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
     const bool aligned = (uintptr_t)dA % 16 == 0 && (batch == 1 || a_batch_stride % 2 == 0);
     const bool f16 = !transpose_out && aligned && f16_site(prec, M, K1, K2);
     int w_exp = 0;
-    if (f16) {  // the halves hold components below 1
+    if (f16 && prec != PSIM_BF16X3) {  // the halves hold components below 1
       double mx = 0;
       for (const cd& w : Wc)
         for (double v : {std::abs(w.real()), std::abs(w.imag())})
@@ -214,8 +214,8 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
       if (mx > 0) std::frexp(mx, &w_exp);
       for (cd& w : Wc) w = cd(std::ldexp(w.real(), -w_exp), std::ldexp(w.imag(), -w_exp));
     }
-    pack_site_matrix(prec == PSIM_BF16X3 ? PSIM_FP32_4M : f16 ? PSIM_FP32_3M : prec, Wc.data(), K, N, packed, ld);
-    if (prec == PSIM_BF16X3) pack_site_matrix_bf16(Wc.data(), K, N, packed_b, ld_b, plane_b);
+    pack_site_matrix(f16 ? PSIM_FP32_3M : prec == PSIM_BF16X3 ? PSIM_FP32_4M : prec, Wc.data(), K, N, packed, ld);
+    if (prec == PSIM_BF16X3 && !f16) pack_site_matrix_bf16(Wc.data(), K, N, packed_b, ld_b, plane_b);
     void* dW = nullptr;
     void* dWb = nullptr;
     hip_check(hipMalloc(&dW, packed.size() + packed_b.size() + (f16 ? (size_t)batch * 4 : 0)), "hipMalloc(W)");
@@ -247,13 +247,15 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
       g.split = split;
       g.cfg = transpose_out ? 0 : cfg;
       if (f16) {
-        uint32_t* amax = (uint32_t*)((char*)dW + packed.size());
-        launch_pack_w_f16(dW, dW, (int64_t)(packed.size() / 128), st);
-        launch_exponents_f16(dA, K1 * M * K2, batch > 1 ? a_batch_stride : K1 * M * K2, batch, amax, st);
-        g.f16 = 1;
-        g.amax_in = amax;
+        launch_pack_w_f16(dW, dW, (int64_t)(packed.size() / 128), st, prec == PSIM_BF16X3);
+        g.f16 = prec == PSIM_BF16X3 ? 2 : 1;
         g.w_exp = w_exp;
         if (batch == 1) g.sA_node = K1 * M * K2;
+        if (g.f16 == 1) {
+          uint32_t* amax = (uint32_t*)((char*)dW + packed.size());
+          launch_exponents_f16(dA, K1 * M * K2, batch > 1 ? a_batch_stride : K1 * M * K2, batch, amax, st);
+          g.amax_in = amax;
+        }
       }
       launch_site_gemm(g, st);
       hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");

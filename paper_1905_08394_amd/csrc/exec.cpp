@@ -160,7 +160,10 @@ void tune_plan(psim_plan_t* pl, void* ws, size_t ws_bytes, void* stream, int rep
     g.W0 = g.W1 = dm.ptr;
     g.ldw = dm.ld;
     g.f16 = dm.f16;
-    if (dm.ptr_b) {  // BF16x3: the pre-split planes
+    if (dm.f16 && dm.ptr_b) {  // BF16x3: the pre-split pairs
+      g.W0 = g.W1 = dm.ptr_b;
+      g.f16 = 2;
+    } else if (dm.ptr_b) {  // the pre-split planes
       g.Wb0 = g.Wb1 = dm.ptr_b;
       g.ldwb = dm.ld_b;
       g.planeb = dm.plane_b;
@@ -398,7 +401,7 @@ void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
               if (g.split && !split_candidate(prec, g.cfg)) g.cfg = 0;  // the split kernels' tiles
             }
             if (bf16_companion) g.prec = PSIM_FP32_4M;           // the FP32 4M matrices every BF16x3 site has
-            if (s.kind == 1 && w0m.ptr_b && !bf16_companion) {
+            if (s.kind == 1 && w0m.ptr_b && !w0m.f16 && !bf16_companion) {
               g.Wb0 = w0m.ptr_b;
               g.Wb1 = w1m.ptr_b;
               g.ldwb = w0m.ld_b;
@@ -407,7 +410,11 @@ void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
             g.W0 = w0m.ptr;
             g.W1 = w1m.ptr;
             g.ldw = w0m.ld;
-            if (s.amax >= 0) {
+            if (s.amax >= 0 && prec == PSIM_BF16X3 && !bf16_companion) {
+              g.f16 = 2;
+              g.W0 = w0m.ptr_b;
+              g.W1 = w1m.ptr_b;
+            } else if (s.amax >= 0) {
               g.f16 = 1;
               g.a_exp = a_exp;
               g.amax_in = a_max;

@@ -579,10 +579,9 @@ __global__ __launch_bounds__(256) void site_gemm_group(GroupArgs ga) {
 
 // ---------------------------------------------------------------- 4M, direct-to-LDS
 // The interior-site contraction for launches where every tile is interior and
-// every stage lies inside one k1 block (the ROWFAST conditions): FP64 plans on
-// v_mfma_f64_16x16x4f64, and the FP32 companion sweep of BF16x3 plans on
-// v_mfma_f32_32x32x2f32 (FP32 4M and 3M plans run these shapes on the
-// half-precision units, site_f16.hip).  Operands are copied global -> LDS by
+// every stage lies inside one k1 block (the ROWFAST conditions) of FP64 plans,
+// on v_mfma_f64_16x16x4f64 (FP32 and BF16x3 plans run these shapes on the
+// 16-bit units, site_f16.hip).  Operands are copied global -> LDS by
 // the load unit itself (global_load_lds_dwordx4): no register staging and no
 // LDS store instructions.  Each wave-wide copy writes 64 x 16 bytes
 // contiguously, so the LDS tiles are unpadded rows of 128 bytes (8 chunks of
@@ -720,7 +719,8 @@ __global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
 }
 
 // ---------------------------------------------------------------- BF16x3
-// Split-precision variant of the 4M kernel for row-major A and a plain store:
+// Split-precision variant of the 4M kernel for row-major A and a plain store,
+// for the shapes that site_f16.hip does not take (K not a multiple of 16):
 // every FP32 operand x is split as x = hi + lo with hi = bf16(x) and
 // lo = bf16(x - hi) (round to nearest even), and
 //   a b ~= a_hi b_hi + a_hi b_lo + a_lo b_hi
@@ -731,7 +731,7 @@ __global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-template <int BM, int BN, bool FAST>
+template <int BM, int BN>
 __global__ __launch_bounds__(256) void site_gemm_bf16x3(KArgs p) {
   constexpr int BK = 16;                 // reals per stage: one MFMA k-step
   constexpr int LD = BK + 8;             // padded LDS row (bf16), 48 bytes
@@ -780,35 +780,19 @@ __global__ __launch_bounds__(256) void site_gemm_bf16x3(KArgs p) {
   };
   Stage set0, set1;
 
-  long long fk1 = 0, fk2 = 0;  // FAST: next stage's (k1, k2), as in ROWFAST; loads are issued in stage order
   auto load = [&](long long kr0, Stage& r) {
-    if constexpr (FAST) {  // interior tile, stage inside one k1 (see ROWFAST)
-      const float* base = A + 2 * (fk1 * sK1 + m0 * p.K2 + fk2);
 #pragma unroll
-      for (int it = 0; it < A_VECS; ++it) {
-        const int lin = it * 256 + tid;
-        const int row = lin / (BK / 4), kq = lin % (BK / 4);
-        r.a[it] = *(const f32x4*)(base + 2 * (long long)row * p.K2 + kq * 4);
+    for (int it = 0; it < A_VECS; ++it) {
+      const int lin = it * 256 + tid;
+      const int row = lin / (BK / 4), kq = lin % (BK / 4);
+      const long long m = m0 + row, kr = kr0 + kq * 4;
+      f32x4 v = {};
+      if (m < p.M && kr < p.Kr) {
+        const unsigned k = (unsigned)(kr >> 1);
+        const unsigned k1 = k / K2u, k2 = k - k1 * K2u;
+        v = *(const f32x4*)(A + 2 * ((long long)k1 * sK1 + m * p.K2 + k2));
       }
-      fk2 += BK / 2;
-      if (fk2 == p.K2) {
-        fk2 = 0;
-        ++fk1;
-      }
-    } else {
-#pragma unroll
-      for (int it = 0; it < A_VECS; ++it) {
-        const int lin = it * 256 + tid;
-        const int row = lin / (BK / 4), kq = lin % (BK / 4);
-        const long long m = m0 + row, kr = kr0 + kq * 4;
-        f32x4 v = {};
-        if (m < p.M && kr < p.Kr) {
-          const unsigned k = (unsigned)(kr >> 1);
-          const unsigned k1 = k / K2u, k2 = k - k1 * K2u;
-          v = *(const f32x4*)(A + 2 * ((long long)k1 * sK1 + m * p.K2 + k2));
-        }
-        r.a[it] = v;
-      }
+      r.a[it] = v;
     }
 #pragma unroll
     for (int it = 0; it < B_VECS; ++it) {
@@ -909,197 +893,6 @@ __global__ __launch_bounds__(256) void site_gemm_bf16x3(KArgs p) {
         const long long row = m0 + wr * WM + bi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         const long long col = n0 + wc * WN + bj * 32 + (lane & 31);
         if (row < p.M && col < p.Nr) C[row * p.Nr + col] = acc[bi][bj][r];
-      }
-}
-
-// Direct-to-LDS form of the BF16x3 kernel for interior launches (every tile
-// interior, every 16-real stage inside one k1 block, a multiple of four
-// stages).  A is copied global -> LDS in FP32 by the load unit and split into
-// hi / lo as its fragments are read; W's two pre-split planes are copied side
-// by side into one 64-byte LDS row per output column (hi k 0..15, then lo
-// k 0..15).  Rows are unpadded, their four 16-byte chunks permuted by
-// (row >> 2) & 3 so the fragment reads of 16 consecutive rows hit distinct
-// banks.  Four LDS buffers form a ring: the copies of a stage are issued
-// three stages before its products, so about 2 us of matrix work covers the
-// latency of a copy that misses L2.  512 threads: 8 waves as 4 (m) x 2 (n)
-// blocks of 64 x 128 outputs, 128 accumulator registers each, two waves per
-// SIMD.  The split, the products and their order for each output element
-// are those of site_gemm_bf16x3, so the two agree bit for bit.
-// x = hi + lo for 8 floats (x0 then x1) with hi = bf16(x) and lo =
-// bf16(x - hi), both rounded to nearest even, as the operand registers of a
-// 32x32x16 MFMA hold them.  Each pair is rounded in one packed conversion and
-// its hi values are widened back to FP32 by a shift and a mask of the packed
-// word (bf16 is the upper half of an FP32), so x - hi is exact as in the
-// scalar form.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split_bf16x8(const f32x4 x0, const f32x4 x1, bf16x8& hi, bf16x8& lo) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const f32x4& x = q < 2 ? x0 : x1;
-    const int e = 2 * (q & 1);
-    const bf16x2 h = __builtin_convertvector(f32x2{x[e], x[e + 1]}, bf16x2);
-    const unsigned u = __builtin_bit_cast(unsigned, h);
-    const float f0 = __builtin_bit_cast(float, u << 16), f1 = __builtin_bit_cast(float, u & 0xffff0000u);
-    const bf16x2 l = __builtin_convertvector(f32x2{x[e] - f0, x[e + 1] - f1}, bf16x2);
-    hi[2 * q] = h[0];
-    hi[2 * q + 1] = h[1];
-    lo[2 * q] = l[0];
-    lo[2 * q + 1] = l[1];
-  }
-}
-
-__device__ __forceinline__ int ring_swz(int r) { return (r >> 2) & 3; }
-
-template <int BM, int BN>
-__global__ __launch_bounds__(512) void site_gemm_bf16x3_dtl(KArgs p) {
-  constexpr int BK = 16;                 // reals per stage: one MFMA k-step
-  constexpr int NW = 8;                  // waves per workgroup
-  constexpr int WM = BM / 4, WN = BN / 2;
-  constexpr int MBLK = WM / 32, NBLK = WN / 32;
-  constexpr int A_INS = BM * 64 / 1024 / NW;  // wave-wide 1 KiB copies per wave and stage
-  constexpr int B_INS = BN * 64 / 1024 / NW;
-  static_assert(A_INS >= 1 && B_INS >= 1 && A_INS * NW * 1024 == BM * 64 && B_INS * NW * 1024 == BN * 64, "tile");
-  __shared__ __attribute__((aligned(1024))) float sA0[BM * BK];
-  __shared__ __attribute__((aligned(1024))) float sA1[BM * BK];
-  __shared__ __attribute__((aligned(1024))) float sA2[BM * BK];
-  __shared__ __attribute__((aligned(1024))) float sA3[BM * BK];
-  __shared__ __attribute__((aligned(1024))) __bf16 sB0[BN * 2 * BK];
-  __shared__ __attribute__((aligned(1024))) __bf16 sB1[BN * 2 * BK];
-  __shared__ __attribute__((aligned(1024))) __bf16 sB2[BN * 2 * BK];
-  __shared__ __attribute__((aligned(1024))) __bf16 sB3[BN * 2 * BK];
-
-  const long long t = xcd_tile(p.T);
-  if (t >= p.T) return;
-  const long long nt = t % p.NT;
-  const long long rest = t / p.NT;
-  const long long mt = rest % p.MT;
-  const long long z = rest / p.MT;
-  const long long node = z / p.Bz, vb = z % p.Bz;
-  const long long ablk = p.a_index ? (long long)p.a_index[node] : node;
-  const float* __restrict__ A = (const float*)p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
-  const int tauv = p.tau ? (int)p.tau[node * p.tau_stride] : 0;
-  const __bf16* __restrict__ Wh = (const __bf16*)(tauv ? p.W1 : p.W0) + p.w_koff_r;
-  const __bf16* __restrict__ Wl = Wh + p.plane;
-  float* __restrict__ C = (float*)p.C + 2 * (node * p.sC_node + vb * p.sC_v);
-  const long long m0 = mt * BM, n0 = nt * BN;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wid = tid >> 6;
-  const int wr = wid >> 1, wc = wid & 1;
-  const long long sK1 = p.M * p.K2;
-
-  // Copy `it` of this wave fills tile rows (it * NW + wid) * 16 + lane / 4,
-  // physical chunk lane % 4, from logical chunk (lane % 4) ^ swz(row); for W
-  // logical chunks 0-1 are the hi plane's k 0..15 and 2-3 the lo plane's.
-  // Byte offsets from the uniform stage bases stay below 2^31.
-  const unsigned a_rs = (unsigned)(2 * p.K2 * 4);  // bytes between rows of A
-  const unsigned b_rs = (unsigned)(p.ldw * 2);     // bytes between rows of a W plane
-  long long fk1 = 0, fk2 = 0, kr = 0;              // next stage: (k1, k2) of A, real k of W
-  auto issue = [&](float* sa, __bf16* sb) {
-    const char* abase = (const char*)(A + 2 * (fk1 * sK1 + m0 * p.K2 + fk2));
-    const char* hbase = (const char*)(Wh + n0 * p.ldw + kr);
-    const char* lbase = (const char*)(Wl + n0 * p.ldw + kr);
-#pragma unroll
-    for (int it = 0; it < A_INS; ++it) {
-      const int row = (it * NW + wid) * 16 + (lane >> 2);
-      const int chk = (lane & 3) ^ ring_swz(row);
-      __builtin_amdgcn_global_load_lds((const void*)(abase + (unsigned)row * a_rs + (unsigned)chk * 16u),
-                                       PSIM_LDS(sa + (it * NW + wid) * 256), 16, 0, 0);
-    }
-#pragma unroll
-    for (int it = 0; it < B_INS; ++it) {
-      const int row = (it * NW + wid) * 16 + (lane >> 2);
-      const int chk = (lane & 3) ^ ring_swz(row);
-      const char* src = ((chk & 2) ? lbase : hbase) + (unsigned)row * b_rs + (unsigned)(chk & 1) * 16u;
-      __builtin_amdgcn_global_load_lds((const void*)src, PSIM_LDS(sb + (it * NW + wid) * 512), 16, 0, 0);
-    }
-    fk2 += BK / 2;
-    if (fk2 == p.K2) {
-      fk2 = 0;
-      ++fk1;
-    }
-    kr += BK;
-  };
-
-  f32x16 acc[MBLK][NBLK];
-#pragma unroll
-  for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NBLK; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0;
-
-  const int frow = lane & 31, h = lane >> 5;  // lane half h supplies k 8h .. 8h+7 of the k-step
-  auto compute = [&](const float* a_s, const __bf16* b_s) {
-    bf16x8 ah[MBLK], al[MBLK], bh[NBLK], bl[NBLK];
-#pragma unroll
-    for (int bi = 0; bi < MBLK; ++bi) {
-      const int r = wr * WM + bi * 32 + frow;
-      const int sw = ring_swz(r);
-      const f32x4 x0 = *(const f32x4*)(a_s + r * BK + (((2 * h) ^ sw) << 2));
-      const f32x4 x1 = *(const f32x4*)(a_s + r * BK + (((2 * h + 1) ^ sw) << 2));
-      split_bf16x8(x0, x1, ah[bi], al[bi]);
-    }
-#pragma unroll
-    for (int bj = 0; bj < NBLK; ++bj) {
-      const int r = wc * WN + bj * 32 + frow;
-      const int sw = ring_swz(r);
-      bh[bj] = *(const bf16x8*)(b_s + r * 2 * BK + ((h ^ sw) << 3));
-      bl[bj] = *(const bf16x8*)(b_s + r * 2 * BK + (((2 + h) ^ sw) << 3));
-    }
-#pragma unroll
-    for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[bi], bh[bj], acc[bi][bj], 0, 0, 0);
-        acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[bi], bl[bj], acc[bi][bj], 0, 0, 0);
-        acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[bi], bh[bj], acc[bi][bj], 0, 0, 0);
-      }
-  };
-  // vmcnt(n), other counters unconstrained: all but this wave's n most recent
-  // copies into LDS have landed (A_INS + B_INS copies per stage)
-  constexpr int PER = A_INS + B_INS;
-  static_assert(2 * PER <= 15, "vmcnt field");
-  constexpr unsigned kWaitVm0 = 0x3f70, kWaitVm1 = 0x3f70 | PER, kWaitVm2 = 0x3f70 | (2 * PER);
-
-  // one stage: wait for its copies (the copies of up to two later stages
-  // may still be in flight), barrier (every wave's copies have landed and
-  // every wave is done with the buffer the next issue overwrites), issue the
-  // copies of stage s + 3 into that buffer, then the stage's products
-  const int nst = (int)(p.Kr / BK);  // the launcher guarantees a multiple of 4
-#define PSIM_BF16X3_RING(S, SA, SB, NA, NB)                     \
-  {                                                             \
-    const int s_ = (S);                                         \
-    if (s_ + 2 < nst)                                           \
-      __builtin_amdgcn_s_waitcnt(kWaitVm2);                     \
-    else if (s_ + 1 < nst)                                      \
-      __builtin_amdgcn_s_waitcnt(kWaitVm1);                     \
-    else                                                        \
-      __builtin_amdgcn_s_waitcnt(kWaitVm0);                     \
-    __syncthreads();                                            \
-    if (s_ + 3 < nst) issue(NA, NB);                            \
-    compute(SA, SB);                                            \
-  }
-  issue(sA0, sB0);
-  issue(sA1, sB1);
-  issue(sA2, sB2);
-  for (int s0 = 0; s0 < nst; s0 += 4) {
-    PSIM_BF16X3_RING(s0, sA0, sB0, sA3, sB3)
-    PSIM_BF16X3_RING(s0 + 1, sA1, sB1, sA0, sB0)
-    PSIM_BF16X3_RING(s0 + 2, sA2, sB2, sA1, sB1)
-    PSIM_BF16X3_RING(s0 + 3, sA3, sB3, sA2, sB2)
-  }
-#undef PSIM_BF16X3_RING
-
-#pragma unroll
-  for (int bi = 0; bi < MBLK; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NBLK; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const long long row = m0 + wr * WM + bi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const long long col = n0 + wc * WN + bj * 32 + (lane & 31);
-        if (col < p.Nr) C[row * p.Nr + col] = acc[bi][bj][r];
       }
 }
 
@@ -1354,8 +1147,8 @@ int fp32_3m_config_count() { return (int)(sizeof(kFp32_3mConfigs) / sizeof(kFp32
 // FP64 candidates: 0 = direct-to-LDS 128 x 64, 1 = direct-to-LDS 64 x 64,
 // 2 = row-major 128 x 64 x 16 (LDS through registers)
 int fp64_config_count() { return 3; }
-// BF16x3 candidates: 0 = 256 x 256 tiles, 1 = 128 x 256, 2 = the direct-to-LDS
-// kernel with 256 x 256 tiles and two waves per SIMD
+// BF16x3 candidates: 0 = 256 x 256 tiles, 1 = 128 x 256, 2 = as 0 (for the
+// shapes that do not go to site_f16.hip)
 int bf16x3_config_count() { return 3; }
 int config_count(int prec) {
   switch (prec) {
@@ -1436,7 +1229,8 @@ int group_variant(const GemmLaunch& g, void* out, long long* tiles) {
     bm = 256;
     bn = 64;
   } else {
-    if (mode == ROWMAJOR && g.M % 128 == 0 && (2 * g.K1 * g.K2) % 32 == 0 && (2 * g.K2) % 32 == 0) mode = ROWFAST;
+    if (g.trans_out && mode == ROWMAJOR && g.M % 128 == 0 && (2 * g.K1 * g.K2) % 32 == 0 && (2 * g.K2) % 32 == 0)
+      mode = ROWFAST;
     id = 8 * (g.prec == PSIM_FP32_3M ? 1 : 0) + 2 * mode + (g.trans_out ? 1 : 0);
     bm = 128;
     bn = 128;
@@ -1461,7 +1255,7 @@ static void glaunch_mode(int mode, bool trans, const GroupArgs& ga, long long bl
     case ROWMAJOR: trans ? glaunch<SCH, ROWMAJOR, true>(ga, blocks, st) : glaunch<SCH, ROWMAJOR, false>(ga, blocks, st); break;
     case KMAJOR: trans ? glaunch<SCH, KMAJOR, true>(ga, blocks, st) : glaunch<SCH, KMAJOR, false>(ga, blocks, st); break;
     case GENERIC: trans ? glaunch<SCH, GENERIC, true>(ga, blocks, st) : glaunch<SCH, GENERIC, false>(ga, blocks, st); break;
-    default: trans ? glaunch<SCH, ROWFAST, true>(ga, blocks, st) : glaunch<SCH, ROWFAST, false>(ga, blocks, st); break;
+    default: glaunch<SCH, ROWFAST, true>(ga, blocks, st); break;
   }
 }
 
@@ -1567,9 +1361,10 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
     const long long blocks = (b.T + 7) / 8 * 8;
     if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
     const int mode = fp32_mode(g);
-    // interior-only tiles of bm rows and bk reals per stage
+    // transposed stores, interior-only tiles of bm rows and bk reals per stage
+    // (plain stores of such shapes run on the 16-bit units, site_f16.hip)
     auto fast = [&](int bm, int bk) {
-      return mode == ROWMAJOR && g.M % bm == 0 && (2 * g.K1 * g.K2) % bk == 0 && (2 * g.K2) % bk == 0;
+      return g.trans_out && mode == ROWMAJOR && g.M % bm == 0 && (2 * g.K1 * g.K2) % bk == 0 && (2 * g.K2) % bk == 0;
     };
     if (g.split && g.prec == PSIM_FP32_4M) {
       if (g.trans_out && g.N <= 32 && fast(128, 32)) {
@@ -1583,8 +1378,7 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
         if (fb > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
         launch<float, 128, 64, 32, ROWFAST, true, 4, true>(f, fb, st);
       } else if (fast(128, 32))
-        g.trans_out ? launch<float, 128, 128, 32, ROWFAST, true, 4, true>(b, blocks, st)
-                    : launch<float, 128, 128, 32, ROWFAST, false, 4, true>(b, blocks, st);
+        launch<float, 128, 128, 32, ROWFAST, true, 4, true>(b, blocks, st);
       else if (mode == ROWMAJOR)
         g.trans_out ? launch<float, 128, 128, 32, ROWMAJOR, true, 4, true>(b, blocks, st)
                     : launch<float, 128, 128, 32, ROWMAJOR, false, 4, true>(b, blocks, st);
@@ -1597,8 +1391,7 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
     } else if (g.split && g.prec == PSIM_FP32_3M) {
       // per-stage partial sums
       if (fast(128, 32))
-        g.trans_out ? launch<float, 128, 128, 32, ROWFAST, true, 3, true>(b, blocks, st)
-                    : launch<float, 128, 128, 32, ROWFAST, false, 3, true>(b, blocks, st);
+        launch<float, 128, 128, 32, ROWFAST, true, 3, true>(b, blocks, st);
       else if (mode == ROWMAJOR)
         g.trans_out ? launch<float, 128, 128, 32, ROWMAJOR, true, 3, true>(b, blocks, st)
                     : launch<float, 128, 128, 32, ROWMAJOR, false, 3, true>(b, blocks, st);
@@ -1629,22 +1422,10 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
       b.T = b.MT * b.NT * Z;
       const long long bl = (b.T + 7) / 8 * 8;
       if (bl > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-      const bool f = g.M % bm == 0 && (2 * g.K1 * g.K2) % 16 == 0 && (2 * g.K2) % 16 == 0;
-      // candidate 2: the direct-to-LDS form (16-real stages inside one k1
-      // block, a multiple of four of them, 32-bit copy offsets); other
-      // shapes take candidate 0's kernel, which gives the same results
-      const bool dtl = g.cfg == 2 && g.M % 256 == 0 && (2 * g.K2) % 16 == 0 && (2 * g.K1 * g.K2) % 64 == 0 &&
-                       g.K2 < (1 << 20) && g.ldwb < (1 << 22);
-      if (dtl)
-        hipLaunchKernelGGL((site_gemm_bf16x3_dtl<256, 256>), dim3((unsigned)bl), dim3(512), 0, st, b);
-      else if (big && f)
-        hipLaunchKernelGGL((site_gemm_bf16x3<256, 256, true>), dim3((unsigned)bl), dim3(256), 0, st, b);
-      else if (big)
-        hipLaunchKernelGGL((site_gemm_bf16x3<256, 256, false>), dim3((unsigned)bl), dim3(256), 0, st, b);
-      else if (f)
-        hipLaunchKernelGGL((site_gemm_bf16x3<128, 256, true>), dim3((unsigned)bl), dim3(256), 0, st, b);
+      if (big)
+        hipLaunchKernelGGL((site_gemm_bf16x3<256, 256>), dim3((unsigned)bl), dim3(256), 0, st, b);
       else
-        hipLaunchKernelGGL((site_gemm_bf16x3<128, 256, false>), dim3((unsigned)bl), dim3(256), 0, st, b);
+        hipLaunchKernelGGL((site_gemm_bf16x3<128, 256>), dim3((unsigned)bl), dim3(256), 0, st, b);
     } else if (g.prec == PSIM_FP32_3M && !g.trans_out && g.cfg > 0 && !g.split && mode == ROWMAJOR) {
       const FCfg& c = kFp32_3mConfigs[g.cfg];
       b.MT = (b.M + c.bm - 1) / c.bm;
@@ -1652,12 +1433,9 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
       b.T = b.MT * b.NT * Z;
       const long long bl = (b.T + 7) / 8 * 8;
       if (bl > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-      const bool f = fast(c.bm, c.bk);
       switch (g.cfg) {
-        case 1: f ? launch<float, 256, 128, 32, ROWFAST, false, 3>(b, bl, st)
-                  : launch<float, 256, 128, 32, ROWMAJOR, false, 3>(b, bl, st); break;
-        case 2: f ? launch<float, 128, 256, 32, ROWFAST, false, 3>(b, bl, st)
-                  : launch<float, 128, 256, 32, ROWMAJOR, false, 3>(b, bl, st); break;
+        case 1: launch<float, 256, 128, 32, ROWMAJOR, false, 3>(b, bl, st); break;
+        case 2: launch<float, 128, 256, 32, ROWMAJOR, false, 3>(b, bl, st); break;
         case 3:  // 64 x 128 tiles: the split form's only
           launch<float, 128, 128, 32, ROWMAJOR, false, 3>(default_tiles(a, Z), default_blocks(a, Z), st);
           break;
@@ -1665,8 +1443,7 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
       }
     } else if (g.prec == PSIM_FP32_3M) {
       if (fast(128, 32))
-        g.trans_out ? launch<float, 128, 128, 32, ROWFAST, true, 3>(b, blocks, st)
-                    : launch<float, 128, 128, 32, ROWFAST, false, 3>(b, blocks, st);
+        launch<float, 128, 128, 32, ROWFAST, true, 3>(b, blocks, st);
       else if (mode == ROWMAJOR)
         g.trans_out ? launch<float, 128, 128, 32, ROWMAJOR, true, 3>(b, blocks, st)
                     : launch<float, 128, 128, 32, ROWMAJOR, false, 3>(b, blocks, st);
@@ -1684,18 +1461,12 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
       b.T = b.MT * b.NT * Z;
       const long long bl = (b.T + 7) / 8 * 8;
       if (bl > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-      const bool f = fast(c.bm, c.bk);
       switch (g.cfg) {
-        case 1: f ? launch<float, 256, 128, 16, ROWFAST, false>(b, bl, st)
-                  : launch<float, 256, 128, 16, ROWMAJOR, false>(b, bl, st); break;
-        case 2: f ? launch<float, 128, 256, 16, ROWFAST, false>(b, bl, st)
-                  : launch<float, 128, 256, 16, ROWMAJOR, false>(b, bl, st); break;
-        case 3: f ? launch<float, 256, 256, 16, ROWFAST, false>(b, bl, st)
-                  : launch<float, 256, 256, 16, ROWMAJOR, false>(b, bl, st); break;
-        case 4: f ? launch<float, 128, 128, 64, ROWFAST, false>(b, bl, st)
-                  : launch<float, 128, 128, 64, ROWMAJOR, false>(b, bl, st); break;
-        case 5: f ? launch<float, 256, 128, 32, ROWFAST, false>(b, bl, st)
-                  : launch<float, 256, 128, 32, ROWMAJOR, false>(b, bl, st); break;
+        case 1: launch<float, 256, 128, 16, ROWMAJOR, false>(b, bl, st); break;
+        case 2: launch<float, 128, 256, 16, ROWMAJOR, false>(b, bl, st); break;
+        case 3: launch<float, 256, 256, 16, ROWMAJOR, false>(b, bl, st); break;
+        case 4: launch<float, 128, 128, 64, ROWMAJOR, false>(b, bl, st); break;
+        case 5: launch<float, 256, 128, 32, ROWMAJOR, false>(b, bl, st); break;
         case 6:
           launch<float, 128, 128, 32, ROWMAJOR, false>(default_tiles(a, Z), default_blocks(a, Z), st);
           break;
@@ -1712,13 +1483,8 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
         launch<float, 256, 64, 16, ROWMAJOR, true>(b, bl, st);
       else
         launch<float, 256, 64, 16, KMAJOR, true>(b, bl, st);
-    } else if (!g.trans_out && !g.nb && fast(128, 32) && (2 * g.K1 * g.K2) % 64 == 0 && g.K2 < (1 << 20) &&
-               g.ldw < (1 << 22)) {
-      // interior tiles, an even number of K stages: direct-to-LDS 4M kernel
-      hipLaunchKernelGGL((site_gemm_4m_dtl<float, 128, 128, 2>), dim3((unsigned)blocks), dim3(256), 0, st, b);
     } else if (fast(128, 32))
-      g.trans_out ? launch<float, 128, 128, 32, ROWFAST, true>(b, blocks, st)
-                  : launch<float, 128, 128, 32, ROWFAST, false>(b, blocks, st);
+      launch<float, 128, 128, 32, ROWFAST, true>(b, blocks, st);
     else if (mode == ROWMAJOR)
       g.trans_out ? launch<float, 128, 128, 32, ROWMAJOR, true>(b, blocks, st)
                   : launch<float, 128, 128, 32, ROWMAJOR, false>(b, blocks, st);

@@ -539,12 +539,16 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
             hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
             if (dm.f16) launch_pack_w_f16(dm.ptr, dm.ptr, (int64_t)(buf.size() / 128), nullptr);
           }
-          if (opts.prec == PSIM_BF16X3) {  // interior sites also get the split planes
-            pack_site_matrix_bf16(W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld_b, dm.plane_b);
+          if (opts.prec == PSIM_BF16X3) {  // the operands of the plan's own products beside those of its companion sweep
+            if (dm.f16)
+              pack_site_matrix(PSIM_FP32_3M, W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld_b);
+            else
+              pack_site_matrix_bf16(W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld_b, dm.plane_b);
             pl->weights_bytes += buf.size();
             if (!pl->host_only) {
               hip_check(hipMalloc(&dm.ptr_b, buf.size()), "hipMalloc(site matrix)");
               hip_check(hipMemcpy(dm.ptr_b, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
+              if (dm.f16) launch_pack_w_f16(dm.ptr_b, dm.ptr_b, (int64_t)(buf.size() / 128), nullptr, true);
             }
           }
         }

@@ -89,8 +89,8 @@ struct DevMatrix {
   int64_t ld = 0;        // leading dimension (real elements) of the packed layout
   int exp2 = 0;          // site matrix was scaled by 2^-exp2
   bool f16 = false;      // ptr holds W split into halves (site_f16.hip)
-  void* ptr_b = nullptr; // BF16x3 plans: hi and lo bf16 planes of the 4M expansion
-  int64_t ld_b = 0, plane_b = 0;
+  void* ptr_b = nullptr; // BF16x3 plans: f16 sites: W split into bfloat16 pairs; others: hi and lo bf16 planes of
+  int64_t ld_b = 0, plane_b = 0;  // the 4M expansion
 };
 
 }  // namespace psim
@@ -224,7 +224,7 @@ struct GemmLaunch {
   const void* Wb1 = nullptr;
   int64_t ldwb = 0, planeb = 0;
   int64_t ldct = 0;                   // transposed stores: row stride of C^T in complex elements (0 = M)
-  int32_t f16 = 0;                    // FP32 4M / 3M: W0 and W1 are split into halves (site_f16.hip)
+  int32_t f16 = 0;                    // W0 and W1 are split into 1: halves (FP32), 2: bfloat16 pairs (BF16x3); site_f16.hip
   int32_t a_exp = 0, w_exp = 0;       // f16: |components of A| < 2^a_exp (times what amax_in says), W is 2^-w_exp
                                       // times the matrix to contract
   const uint32_t* amax_in = nullptr;  // f16, per node: exponent + 4096 of the largest component of A (0: A is zero)
@@ -247,7 +247,7 @@ std::string tune_key(const std::string& arch, int prec, int64_t M, int64_t K1, i
 bool tune_cache_lookup(const std::string& key, int* cfg);
 void tune_cache_store(const std::map<std::string, std::pair<int, double>>& entries);
 void launch_site_gemm(const GemmLaunch& g, void* stream);
-// site_f16.hip: FP32 contractions on the half-precision matrix units.  A
+// site_f16.hip: FP32 and BF16x3 contractions on the 16-bit matrix units.  A
 // contraction goes there when its matrix was packed for it, which f16_site
 // decides from the shape alone (M: the most rows it is launched with).
 bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2);
@@ -257,7 +257,7 @@ void launch_group_f16(int variant, const void* const* d_probs, const long long* 
 int f16_descriptor_bytes();
 // groups * 16 complex k of packed 3M rows (Re, Im interleaved along k) into
 // the split halves the kernels read, in place or not
-void launch_pack_w_f16(const void* src, void* dst, int64_t groups, void* stream);
+void launch_pack_w_f16(const void* src, void* dst, int64_t groups, void* stream, bool bf16 = false);
 // exponent + 4096 of the largest component of each of `nodes` tensors (0: all zeros)
 void launch_exponents_f16(const void* A, int64_t per_node, int64_t stride, int64_t nodes, uint32_t* out, void* stream);
 // growth of a contraction: |components of C| < 2^growth_exp(K) max |A| max |W|

@@ -1,4 +1,4 @@
-// Site contractions of FP32 plans (4M and 3M) on the half-precision matrix units.
+// Site contractions of FP32 (4M and 3M) and BF16x3 plans on the 16-bit matrix units.
 //
 //   C[m][n] = sum_{k1, k2} A[k1][m][k2] * W[k1*K2 + k2][n]        (complex, eq. S4)
 //
@@ -43,6 +43,14 @@
 // 26.3 -> 13.5, unsplit 23.9 -> 11.0; 64 x (4096, 256, 256) split 0.95 -> 0.49,
 // unsplit 0.89 -> 0.40; 512 x (4096, 64, 64) split 0.81 -> 0.43 (HBM: 5.0
 // TB/s), unsplit 0.68 -> 0.40; 4 x (4096, 4096, 4096) unsplit 12.0 -> 5.7.
+//
+// BF16x3 is the same kernel with bfloat16 pairs (16 significant bits, the FP32
+// range: no scale).  There an instruction sums the Re and Im products of 8 k,
+// which is how the real expansion of the complex matrix orders them (kernels.hip,
+// the shapes left there), so the results are those of that form bit for bit: a
+// last-bit change of an FP32 tensor changes its split, and with it the
+// amplitude, by as much as the precision's own error.  5x5 (1+32+1), 256
+// bitstrings: interior sites 254 -> 189 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,6 +66,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
@@ -94,17 +104,61 @@ constexpr int kTopW = 14;    // W below 2^kTopW (both finite as halves)
 
 __device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 
-__device__ __forceinline__ f16x8 neg(const f16x8 x) {
-  return __builtin_bit_cast(f16x8, __builtin_bit_cast(u32x4, x) ^ 0x80008000u);
+// The two 16-bit types: vectors, the matrix instruction, and the split of two
+// FP32 values (scaled by 2^e) into hi = round(x), lo = round(x - hi).
+template <typename H>
+struct Half;
+
+template <>
+struct Half<_Float16> {
+  typedef f16x2 v2;
+  typedef f16x8 v8;
+  static __device__ __forceinline__ f32x16 mma(v8 a, v8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ void split(float a, float b, int e, float scale, v2& hi, v2& lo) {
+    unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{ldexpf(a, e), ldexpf(b, e)}, v2));
+    // hides the packed conversion from the compiler, which otherwise repeats it
+    // element by element where the halves are used again
+    asm("" : "+v"(u));
+    hi = __builtin_bit_cast(v2, u);
+    lo[0] = (_Float16)fmaf(a, scale, -(float)hi[0]);
+    lo[1] = (_Float16)fmaf(b, scale, -(float)hi[1]);
+  }
+};
+
+// bfloat16 has the FP32 range: no scale
+template <>
+struct Half<__bf16> {
+  typedef bf16x2 v2;
+  typedef bf16x8 v8;
+  static __device__ __forceinline__ f32x16 mma(v8 a, v8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ void split(float a, float b, int, float, v2& hi, v2& lo) {
+    hi = __builtin_convertvector(f32x2{a, b}, v2);
+    const unsigned u = __builtin_bit_cast(unsigned, hi);
+    lo = __builtin_convertvector(f32x2{a - __builtin_bit_cast(float, u << 16),
+                                       b - __builtin_bit_cast(float, u & 0xffff0000u)}, v2);
+  }
+};
+
+// (a, b) pairs to (a, -b) and (b, a)
+template <typename V>
+__device__ __forceinline__ V conj_pairs(const V x) {
+  return __builtin_bit_cast(V, __builtin_bit_cast(u32x4, x) ^ 0x80000000u);
+}
+template <typename V>
+__device__ __forceinline__ V swap_pairs(const V x) {
+  u32x4 u = __builtin_bit_cast(u32x4, x);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) u[e] = __builtin_amdgcn_alignbit(u[e], u[e], 16);
+  return __builtin_bit_cast(V, u);
 }
 
-// Two FP32 values to halves in one packed conversion.  The register is hidden
-// from the compiler, which otherwise repeats the conversion element by element
-// where the halves are used again.
-__device__ __forceinline__ f16x2 round2(float a, float b) {
-  unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, f16x2));
-  asm("" : "+v"(u));
-  return __builtin_bit_cast(f16x2, u);
+template <typename V>
+__device__ __forceinline__ V neg(const V x) {
+  return __builtin_bit_cast(V, __builtin_bit_cast(u32x4, x) ^ 0x80008000u);
 }
 
 // Raises *slot to the exponent + 4096 of the wave's largest m (m >= 0 in every
@@ -121,8 +175,10 @@ __device__ __forceinline__ void raise_exponent(float m, uint32_t* slot) {
 
 #define PSIM_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
-template <int WVM, int WVN, int MBLK, int NBLK, bool SPLIT>
+template <typename H, int WVM, int WVN, int MBLK, int NBLK, bool SPLIT>
 __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long t) {
+  typedef typename Half<H>::v8 v8;
+  constexpr bool PLANAR = __is_same(H, _Float16);  // else bfloat16
   constexpr int NW = WVM * WVN;
   constexpr int BM = WVM * MBLK * 32, BN = WVN * NBLK * 32;
   constexpr int A_INS = BM / 8 / NW, B_INS = BN / 8 / NW;   // wave-wide 1 KB copies (8 rows of 128 bytes)
@@ -143,9 +199,11 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
   const char* __restrict__ W = (const char*)(tauv ? p.W1 : p.W0);
   float* __restrict__ C = p.C + 2 * (node * p.sC_node + vb * p.sC_v);
   const long long m0 = mt * BM;
-  const uint32_t am = p.amax_in ? p.amax_in[node] : 0;
-  const int e_a = p.a_exp + (am ? (int)am - 4096 : 0);
-  const int sa = min(kTop - e_a, 127);
+  int sa = 0;
+  if (PLANAR) {
+    const uint32_t am = p.amax_in ? p.amax_in[node] : 0;
+    sa = min(kTop - p.a_exp - (am ? (int)am - 4096 : 0), 127);
+  }
   const float scale = ldexpf(1.0f, sa);
 
   const int tid = threadIdx.x;
@@ -221,66 +279,109 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
       if constexpr (SPLIT) return part;
       else return acc;
     }();
-    f16x8 w[NBLK][4];  // Re hi, Re lo, Im hi, Im lo
+    // halves: Re hi, Re lo, Im hi, Im lo of the lane's 8 k; bfloat16: hi, lo of
+    // Re and Im in turn, of the lane's 4 k of the stage's first and second 8
+    v8 w[NBLK][4];
 #pragma unroll
     for (int bj = 0; bj < NBLK; ++bj) {
       const int r = (wc * NBLK + bj) * 32 + frow;
       const int sw = swz(r);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) w[bj][q] = *(const f16x8*)(bs + r * 32 + (((2 * q + h) ^ sw) << 2));
+      for (int q = 0; q < 4; ++q) {
+        const int c = PLANAR ? 2 * q + h : 4 * (q & 1) + 2 * (q >> 1) + h;
+        w[bj][q] = *(const v8*)(bs + r * 32 + ((c ^ sw) << 2));
+      }
     }
+#define PSIM_MM(a, b, c) c = Half<H>::mma(a, b, c)
 #pragma unroll
     for (int bi = 0; bi < MBLK; ++bi) {
       const int r = (wr * MBLK + bi) * 32 + frow;
       const int sw = swz(r);
-      f16x8 rh, rl, ih, il;
+      if constexpr (PLANAR) {
+        v8 rh, rl, ih, il;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {  // two complex k per chunk
-        const f32x4 x = *(const f32x4*)(as + r * 32 + (((4 * h + c) ^ sw) << 2));
-        const f16x2 hr = round2(ldexpf(x[0], sa), ldexpf(x[2], sa));
-        const f16x2 hi = round2(ldexpf(x[1], sa), ldexpf(x[3], sa));
+        for (int c = 0; c < 4; ++c) {  // two complex k per chunk
+          const f32x4 x = *(const f32x4*)(as + r * 32 + (((4 * h + c) ^ sw) << 2));
+          typename Half<H>::v2 hr, lr, hi, li;
+          Half<H>::split(x[0], x[2], sa, scale, hr, lr);
+          Half<H>::split(x[1], x[3], sa, scale, hi, li);
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          rh[2 * c + e] = hr[e];
-          ih[2 * c + e] = hi[e];
-          rl[2 * c + e] = (_Float16)fmaf(x[2 * e], scale, -(float)hr[e]);
-          il[2 * c + e] = (_Float16)fmaf(x[2 * e + 1], scale, -(float)hi[e]);
+          for (int e = 0; e < 2; ++e) {
+            rh[2 * c + e] = hr[e];
+            rl[2 * c + e] = lr[e];
+            ih[2 * c + e] = hi[e];
+            il[2 * c + e] = li[e];
+          }
+        }
+        const v8 nh = neg(ih), nl = neg(il);
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj) {
+          PSIM_MM(rl, w[bj][0], dst[bi][bj][0]);
+          PSIM_MM(rl, w[bj][2], dst[bi][bj][1]);
+        }
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj) {
+          PSIM_MM(nl, w[bj][2], dst[bi][bj][0]);
+          PSIM_MM(il, w[bj][0], dst[bi][bj][1]);
+        }
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj) {
+          PSIM_MM(rh, w[bj][1], dst[bi][bj][0]);
+          PSIM_MM(rh, w[bj][3], dst[bi][bj][1]);
+        }
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj) {
+          PSIM_MM(nh, w[bj][3], dst[bi][bj][0]);
+          PSIM_MM(ih, w[bj][1], dst[bi][bj][1]);
+        }
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj) {
+          PSIM_MM(rh, w[bj][0], dst[bi][bj][0]);
+          PSIM_MM(rh, w[bj][2], dst[bi][bj][1]);
+        }
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj) {
+          PSIM_MM(nh, w[bj][2], dst[bi][bj][0]);
+          PSIM_MM(ih, w[bj][0], dst[bi][bj][1]);
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {  // 8 k each: an instruction sums their Re and Im products
+          v8 xh, xl;
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const f32x4 x = *(const f32x4*)(as + r * 32 + (((4 * g + 2 * h + c) ^ sw) << 2));
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              typename Half<H>::v2 hi, lo;
+              Half<H>::split(x[2 * e], x[2 * e + 1], 0, 1.0f, hi, lo);
+              xh[4 * c + 2 * e] = hi[0];
+              xh[4 * c + 2 * e + 1] = hi[1];
+              xl[4 * c + 2 * e] = lo[0];
+              xl[4 * c + 2 * e + 1] = lo[1];
+            }
+          }
+          // (Re, -Im) for Re C, (Im, Re) for Im C
+          const v8 ph = conj_pairs(xh), pl = conj_pairs(xl), qh = swap_pairs(xh), ql = swap_pairs(xl);
+#pragma unroll
+          for (int bj = 0; bj < NBLK; ++bj) {
+            PSIM_MM(pl, w[bj][2 * g], dst[bi][bj][0]);
+            PSIM_MM(ql, w[bj][2 * g], dst[bi][bj][1]);
+          }
+#pragma unroll
+          for (int bj = 0; bj < NBLK; ++bj) {
+            PSIM_MM(ph, w[bj][2 * g + 1], dst[bi][bj][0]);
+            PSIM_MM(qh, w[bj][2 * g + 1], dst[bi][bj][1]);
+          }
+#pragma unroll
+          for (int bj = 0; bj < NBLK; ++bj) {
+            PSIM_MM(ph, w[bj][2 * g], dst[bi][bj][0]);
+            PSIM_MM(qh, w[bj][2 * g], dst[bi][bj][1]);
+          }
         }
       }
-      const f16x8 nh = neg(ih), nl = neg(il);
-#define PSIM_MM(a, b, c) c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0)
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        PSIM_MM(rl, w[bj][0], dst[bi][bj][0]);
-        PSIM_MM(rl, w[bj][2], dst[bi][bj][1]);
-      }
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        PSIM_MM(nl, w[bj][2], dst[bi][bj][0]);
-        PSIM_MM(il, w[bj][0], dst[bi][bj][1]);
-      }
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        PSIM_MM(rh, w[bj][1], dst[bi][bj][0]);
-        PSIM_MM(rh, w[bj][3], dst[bi][bj][1]);
-      }
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        PSIM_MM(nh, w[bj][3], dst[bi][bj][0]);
-        PSIM_MM(ih, w[bj][1], dst[bi][bj][1]);
-      }
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        PSIM_MM(rh, w[bj][0], dst[bi][bj][0]);
-        PSIM_MM(rh, w[bj][2], dst[bi][bj][1]);
-      }
-#pragma unroll
-      for (int bj = 0; bj < NBLK; ++bj) {
-        PSIM_MM(nh, w[bj][2], dst[bi][bj][0]);
-        PSIM_MM(ih, w[bj][0], dst[bi][bj][1]);
-      }
-#undef PSIM_MM
     }
+#undef PSIM_MM
     if (SPLIT && close) {
 #pragma unroll
       for (int bi = 0; bi < MBLK; ++bi)
@@ -309,7 +410,7 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
   }
   if (s < nst) compute(sA0, sB0, true, true);
 
-  const int sc = p.w_exp - sa - kTopW;
+  const int sc = PLANAR ? p.w_exp - sa - kTopW : p.w_exp;
   float mx = 0;
 #pragma unroll
   for (int bi = 0; bi < MBLK; ++bi)
@@ -328,13 +429,13 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
   if (p.amax_out) raise_exponent(mx, p.amax_out + node);
 }
 
-template <int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
+template <typename H, int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
 __global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16(F16Args p) {
   // XCD-aware order: workgroup b runs on XCD b mod 8; each XCD gets a contiguous range of tiles
   const long long per_xcd = (p.T + 7) / 8;
   const long long t = (long long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (t >= p.T) return;
-  site_f16_body<WVM, WVN, MBLK, NBLK, SPLIT>(p, t);
+  site_f16_body<H, WVM, WVN, MBLK, NBLK, SPLIT>(p, t);
 }
 
 // Several contractions in one grid: problem i owns tiles [start[i],
@@ -346,7 +447,7 @@ struct F16Group {
   int nprob;
 };
 
-template <int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
+template <typename H, int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
 __global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16_group(F16Group ga) {
   const long long total = ga.start[ga.nprob];
   const long long per_xcd = (total + 7) / 8;
@@ -363,30 +464,43 @@ __global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16_group(F16Group g
   int* dst = (int*)&p;
 #pragma unroll
   for (int w = 0; w < (int)(sizeof(F16Args) / 4); ++w) dst[w] = __builtin_amdgcn_readfirstlane(src[w]);
-  site_f16_body<WVM, WVN, MBLK, NBLK, SPLIT>(p, g - ga.start[lo]);
+  site_f16_body<H, WVM, WVN, MBLK, NBLK, SPLIT>(p, g - ga.start[lo]);
 }
 
 // Packed FP32 rows (Re, Im interleaved along k, groups of 16 complex k = 128
-// bytes) to Re hi, Re lo, Im hi, Im lo halves of the same 16 k, scaled by
-// 2^kTopW.  One thread per group, so src and dst may be the same.
+// bytes) to halves of the same 16 k, scaled by 2^kTopW: Re hi, Re lo, Im hi, Im
+// lo; or to bfloat16: all hi, all lo, Re and Im in turn.  One thread per group,
+// so src and dst may be the same.
+template <typename H>
 __global__ void pack_w_f16(const float* src, float* dst, long long groups) {
+  typedef typename Half<H>::v8 v8;
+  constexpr bool planar = __is_same(H, _Float16);
+  constexpr int e = planar ? kTopW : 0;
   for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < groups;
        g += (long long)gridDim.x * blockDim.x) {
     f32x4 x[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) x[c] = *(const f32x4*)(src + 32 * g + 4 * c);
-    f16x8 o[8];
+    v8 o[8];
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
+    for (int k = 0; k < 16; k += 2)
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const float y = ldexpf(x[k >> 1][2 * (k & 1) + q], kTopW);
-        const _Float16 hi = (_Float16)y;
-        o[4 * q + (k >> 3)][k & 7] = hi;
-        o[4 * q + 2 + (k >> 3)][k & 7] = (_Float16)(y - (float)hi);
+        const f32x4 v = x[k >> 1];
+        typename Half<H>::v2 hi, lo;
+        if (planar)  // Re (q = 0) or Im of k, k + 1
+          Half<H>::split(v[q], v[2 + q], e, ldexpf(1.0f, e), hi, lo);
+        else         // Re, Im of k + q
+          Half<H>::split(v[2 * q], v[2 * q + 1], e, 1.0f, hi, lo);
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+          const int ch = planar ? 4 * q + (k >> 3) : k >> 2, at = planar ? (k & 7) + d : 2 * ((k & 3) + q) + d;
+          o[ch][at] = hi[d];
+          o[ch + (planar ? 2 : 4)][at] = lo[d];
+        }
       }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) *(f16x8*)(dst + 32 * g + 4 * c) = o[c];
+    for (int c = 0; c < 8; ++c) *(v8*)(dst + 32 * g + 4 * c) = o[c];
   }
 }
 
@@ -412,10 +526,10 @@ __global__ __launch_bounds__(256) void exponents_f16(const float* __restrict__ A
 
 }  // namespace
 
-void launch_pack_w_f16(const void* src, void* dst, int64_t groups, void* stream) {
+void launch_pack_w_f16(const void* src, void* dst, int64_t groups, void* stream, bool bf16) {
   const long long b = std::max<long long>(1, std::min<long long>((groups + 255) / 256, 1 << 16));
-  hipLaunchKernelGGL(pack_w_f16, dim3((unsigned)b), dim3(256), 0, (hipStream_t)stream, (const float*)src, (float*)dst,
-                     (long long)groups);
+  hipLaunchKernelGGL(bf16 ? pack_w_f16<__bf16> : pack_w_f16<_Float16>, dim3((unsigned)b), dim3(256), 0,
+                     (hipStream_t)stream, (const float*)src, (float*)dst, (long long)groups);
   hip_check(hipGetLastError(), "pack_w_f16 launch");
 }
 
@@ -435,7 +549,7 @@ void launch_exponents_f16(const void* A, int64_t per_node, int64_t stride, int64
 // offsets from a stage's base are 32-bit: 128 rows of A, and for a small K2
 // 16 / K2 blocks of M rows.
 bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2) {
-  return (prec == PSIM_FP32_4M || prec == PSIM_FP32_3M) && K2 % 2 == 0 && (K1 * K2) % 16 == 0 &&
+  return prec != PSIM_FP64 && K2 % 2 == 0 && (K1 * K2) % 16 == 0 &&
          (K2 % 16 == 0 || 16 % K2 == 0) && (K2 < 16 ? M < (1 << 24) : K2 < (1 << 21)) && K1 * K2 < (1 << 21);
 }
 
@@ -443,10 +557,11 @@ bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2) {
 //   0: 128 x 128 complex outputs, 4 waves of 64 x 64, two workgroups per CU
 //   1: 128 x 64, 4 waves of 32 x 64, three workgroups per CU
 //   2: the same with partial sums, two workgroups per CU
+//   3, 4: 0 and 1 for BF16x3
 static int f16_variant(const GemmLaunch& g) {
-  if (g.split) return 2;
+  if (g.split && g.f16 == 1) return 2;
   const long long big = ((g.M + 127) / 128) * ((g.N + 127) / 128) * g.nodes * g.Bz;
-  return g.N % 128 == 0 && big >= 1024 ? 0 : 1;
+  return (g.N % 128 == 0 && big >= 1024 ? 0 : 1) + (g.f16 == 2 ? 3 : 0);
 }
 
 static F16Args f16_args(const GemmLaunch& g, int variant) {
@@ -478,7 +593,7 @@ static F16Args f16_args(const GemmLaunch& g, int variant) {
   a.nst = (int)(g.K1 * g.K2 / 16);
   a.a_exp = g.a_exp;
   a.w_exp = g.w_exp;
-  const int bn = variant == 0 ? 128 : 64;
+  const int bn = variant % 3 == 0 ? 128 : 64;
   a.MT = (a.M + 127) / 128;
   a.NT = (a.N + bn - 1) / bn;
   a.T = a.MT * a.NT * g.nodes * g.Bz;
@@ -493,9 +608,11 @@ void launch_site_f16(const GemmLaunch& g, void* stream) {
   if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
   const dim3 grid((unsigned)blocks), wg(256);
   switch (variant) {
-    case 0: hipLaunchKernelGGL((site_f16<2, 2, 2, 2, false, 2>), grid, wg, 0, st, a); break;
-    case 1: hipLaunchKernelGGL((site_f16<4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
-    default: hipLaunchKernelGGL((site_f16<4, 1, 1, 2, true, 2>), grid, wg, 0, st, a); break;
+    case 0: hipLaunchKernelGGL((site_f16<_Float16, 2, 2, 2, 2, false, 2>), grid, wg, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((site_f16<_Float16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((site_f16<_Float16, 4, 1, 1, 2, true, 2>), grid, wg, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((site_f16<__bf16, 2, 2, 2, 2, false, 2>), grid, wg, 0, st, a); break;
+    default: hipLaunchKernelGGL((site_f16<__bf16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
   }
   hip_check(hipGetLastError(), "site_f16 launch");
 }
@@ -512,7 +629,7 @@ int group_variant_f16(const GemmLaunch& g, void* out, long long* tiles) {
 
 void launch_group_f16(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  if (nprob < 1 || nprob > kMaxProbs || variant < 0 || variant > 2) fail(PSIM_EINTERNAL, "bad f16 group");
+  if (nprob < 1 || nprob > kMaxProbs || variant < 0 || variant > 4) fail(PSIM_EINTERNAL, "bad f16 group");
   F16Group ga{};
   for (int i = 0; i < nprob; ++i) {
     ga.probs[i] = (const F16Args*)d_probs[i];
@@ -525,9 +642,11 @@ void launch_group_f16(int variant, const void* const* d_probs, const long long* 
   if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
   const dim3 grid((unsigned)blocks), wg(256);
   switch (variant) {
-    case 0: hipLaunchKernelGGL((site_f16_group<2, 2, 2, 2, false, 2>), grid, wg, 0, st, ga); break;
-    case 1: hipLaunchKernelGGL((site_f16_group<4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
-    default: hipLaunchKernelGGL((site_f16_group<4, 1, 1, 2, true, 2>), grid, wg, 0, st, ga); break;
+    case 0: hipLaunchKernelGGL((site_f16_group<_Float16, 2, 2, 2, 2, false, 2>), grid, wg, 0, st, ga); break;
+    case 1: hipLaunchKernelGGL((site_f16_group<_Float16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
+    case 2: hipLaunchKernelGGL((site_f16_group<_Float16, 4, 1, 1, 2, true, 2>), grid, wg, 0, st, ga); break;
+    case 3: hipLaunchKernelGGL((site_f16_group<__bf16, 2, 2, 2, 2, false, 2>), grid, wg, 0, st, ga); break;
+    default: hipLaunchKernelGGL((site_f16_group<__bf16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
   }
   hip_check(hipGetLastError(), "grouped site_f16 launch");
 }

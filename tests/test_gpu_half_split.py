@@ -119,3 +119,18 @@ def test_strides_alignment_zero_and_non_finite(ps):
         rows = [m for m in range(M) if m != 7]
         assert torch.equal(dirty[rows], clean[rows])
         assert not torch.isfinite(torch.view_as_real(dirty[7])).any()
+
+
+@pytest.mark.parametrize("M,K1,N,batch", [(257, 6, 127, 2), (128, 2, 64, 1), (1, 4, 1, 1), (4096, 2, 256, 16)])
+def test_bf16x3_equals_the_register_staged_kernel(ps, M, K1, N, batch):
+    """BF16x3 on these units against the kernel that takes K = 8 (mod 16): one
+    more k1 of zero products leaves every sum, so the results agree bit for bit."""
+    import torch
+    print(f"bf16x3 M={M} K1={K1} N={N} batch={batch}", flush=True)
+    A, W = _inputs(M, K1, 8, N, batch, np.ones(batch))
+    C = ps.contract_site("bf16x3", torch.from_numpy(A.reshape(-1)).cuda(), W.astype(complex), M, K1, 8, N, batch=batch)
+    A2 = np.concatenate([A, np.zeros_like(A[:, :1])], axis=1)
+    W2 = np.concatenate([W, np.zeros_like(W[:8])], axis=0)
+    C2 = ps.contract_site("bf16x3", torch.from_numpy(A2.reshape(-1)).cuda(), W2.astype(complex), M, K1 + 1, 8, N,
+                          batch=batch)
+    assert torch.equal(C, C2)
