@@ -54,7 +54,7 @@ def log(*a):
 # Source that holds each precision's hot kernel: a file, or the part of it
 # between two "// ----...---- <name>" marker lines; traffic counters are tied to its hash.
 KERNEL_SECTIONS = {"fp32_3m": ("site_f16.hip", None, None),
-                   "fp64": ("kernels.hip", "4M, direct-to-LDS", "BF16x3")}
+                   "fp64": ("kernels.hip", "FP64", "BF16x3")}
 
 
 def kernel_source_hash(prec):

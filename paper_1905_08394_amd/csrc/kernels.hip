@@ -577,40 +577,48 @@ __global__ __launch_bounds__(256) void site_gemm_group(GroupArgs ga) {
   site_gemm_body<T, BM, BN, BK, AMODE, TRANS, SCH, false>(p, g - ga.start[i]);
 }
 
-// ---------------------------------------------------------------- 4M, direct-to-LDS
-// The interior-site contraction for launches where every tile is interior and
-// every stage lies inside one k1 block (the ROWFAST conditions) of FP64 plans,
-// on v_mfma_f64_16x16x4f64 (FP32 and BF16x3 plans run these shapes on the
-// 16-bit units, site_f16.hip).  Operands are copied global -> LDS by
-// the load unit itself (global_load_lds_dwordx4): no register staging and no
-// LDS store instructions.  Each wave-wide copy writes 64 x 16 bytes
-// contiguously, so the LDS tiles are unpadded rows of 128 bytes (8 chunks of
-// 16 bytes; 32 floats or 16 doubles) and the lane that fills physical chunk p
-// of row r fetches logical chunk p ^ swz(r); the fragment reads apply the same
-// permutation, which spreads 16 consecutive rows over distinct banks.  The two
-// LDS buffers are separate arrays and the K loop is unrolled by two, so each
-// copy and each read names its buffer.  BM x BN real outputs per workgroup; a
-// lane's fragment (KV consecutive k) is one chunk.  The products and their
-// order are those of the row-major kernel with the same tile.
+// ---------------------------------------------------------------- FP64
+// FP64 contractions on v_mfma_f64_16x16x4f64, the real expansion of the complex
+// product.  Operands are copied global -> LDS by the load unit itself
+// (global_load_lds_dwordx4): no register staging and no LDS store
+// instructions.  Each wave-wide copy writes 64 x 16 bytes contiguously, so the
+// LDS tiles are unpadded rows of 128 bytes (8 chunks of 16 bytes, one complex k
+// each) and the lane that fills physical chunk p of row r fetches logical chunk
+// p ^ swz(r); the fragment reads apply the same permutation, which spreads 16
+// consecutive rows over distinct banks.  The two LDS buffers are separate arrays
+// and the K loop is unrolled by two, so each copy and each read names its
+// buffer.  BM x BN real outputs per workgroup.
+//
+// GEN false: every tile interior along m, every stage of 8 k inside one k1 block
+// and an even number of them (the hot step: 89 % of the matrix peak).  GEN true:
+// any shape and order.  A chunk is one complex k, so every K2 (1: the first site
+// of a row, A stored [k][m]) is a matter of the lane's address, kept as a
+// running (k2, offset) per copy; rows are clamped to the last one, k past the
+// end is read from the last one and left out of the products.  The shapes it
+// takes (small bonds, ragged sizes, first and last sites) are bound by HBM and
+// latency: a few stages per tile.  Against the form it replaces (one complex at
+// a time through registers into 64 x 64 tiles): last sites of 5x5 (1+32+1), 64
+// bitstrings, 15.8 -> 11.3 ms, first sites 17 ms as before; 4x4 (1+12+1) 256
+// shots 9.6 -> 9.3 ms of kernels (about 5.5 ms of traffic at 4.9 TB/s).
+// TRANS: C^T blocks (the operands of the instruction swapped), so that lanes
+// store along m.
 #define PSIM_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
 __device__ __forceinline__ int dtl_swz(int r) { return (r ^ (r >> 3)) & 7; }
 
-template <typename T, int BM, int BN, int OCC>
-__global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
-  typedef Mfma<T> MF;
-  constexpr int BK = 128 / (int)sizeof(T);  // elements per stage row = 8 chunks
-  constexpr int KV = MF::KV;                 // elements per chunk
+template <int BM, int BN, int OCC, bool GEN, bool TRANS>
+__global__ __launch_bounds__(256, OCC) void site_gemm_f64(KArgs p) {
+  typedef Mfma<double> MF;
+  constexpr int BK = 16;   // reals per stage
   constexpr int WM = BM / 2, WN = BN / 2;
-  constexpr int MBLK = WM / MF::MB, NBLK = WN / MF::MB;
+  constexpr int MBLK = WM / 16, NBLK = WN / 16;
   constexpr int A_INS = BM * 128 / 1024 / 4;
   constexpr int B_INS = BN * 128 / 1024 / 4;
   static_assert(A_INS >= 1 && B_INS >= 1 && MBLK >= 1 && NBLK >= 1, "tile");
-  static_assert(KV * (int)sizeof(T) == 16, "one chunk per fragment");
-  __shared__ __attribute__((aligned(1024))) T sA0[BM * BK];
-  __shared__ __attribute__((aligned(1024))) T sA1[BM * BK];
-  __shared__ __attribute__((aligned(1024))) T sB0[BN * BK];
-  __shared__ __attribute__((aligned(1024))) T sB1[BN * BK];
+  __shared__ __attribute__((aligned(1024))) double sA0[BM * BK];
+  __shared__ __attribute__((aligned(1024))) double sA1[BM * BK];
+  __shared__ __attribute__((aligned(1024))) double sB0[BN * BK];
+  __shared__ __attribute__((aligned(1024))) double sB1[BN * BK];
 
   const long long t = xcd_tile(p.T);
   if (t >= p.T) return;
@@ -620,39 +628,74 @@ __global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
   const long long z = rest / p.MT;
   const long long node = z / p.Bz, vb = z % p.Bz;
   const long long ablk = p.a_index ? (long long)p.a_index[node] : node;
-  const T* __restrict__ A = (const T*)p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
+  const double* __restrict__ A = (const double*)p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
   const int tauv = p.tau ? (int)p.tau[node * p.tau_stride] : 0;
-  const T* __restrict__ W = (const T*)(tauv ? p.W1 : p.W0) + p.w_koff_r;
-  T* __restrict__ C = (T*)p.C + 2 * (node * p.sC_node + vb * p.sC_v);
+  const double* __restrict__ W = (const double*)(tauv ? p.W1 : p.W0) + p.w_koff_r;
+  double* __restrict__ C = (double*)p.C + 2 * (node * p.sC_node + vb * p.sC_v);
   const long long m0 = mt * BM, n0 = nt * BN;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int wr = wid >> 1, wc = wid & 1;
   const long long sK1 = p.M * p.K2;
-  const unsigned a_rs = (unsigned)(2 * p.K2 * (long long)sizeof(T));
-  const unsigned b_rs = (unsigned)(p.ldw * (long long)sizeof(T));
-  auto src_off = [&](int it, unsigned row_stride) {
-    const int row = (it * 4 + wid) * 8 + (lane >> 3);
-    const int chk = (lane & 7) ^ dtl_swz(row);
-    return (unsigned)row * row_stride + (unsigned)chk * 16u;
-  };
+  // row and logical chunk that this lane copies
+  auto row_of = [&](int it) { return (it * 4 + wid) * 8 + (lane >> 3); };
+  auto chunk_of = [&](int it) { return (lane & 7) ^ dtl_swz(row_of(it)); };
+  // GEN false: 32-bit offsets from a uniform stage base
+  const unsigned a_rs = (unsigned)(p.K2 * 16), b_rs = (unsigned)(p.ldw * 8);
   long long fk1 = 0, fk2 = 0, kr = 0;
-  auto issue = [&](T* sa, T* sb) {
-    const char* abase = (const char*)(A + 2 * (fk1 * sK1 + m0 * p.K2 + fk2));
-    const char* bbase = (const char*)(W + n0 * p.ldw + kr);
+  // GEN true: complex k, k2 and offset of each copy's next chunk
+  long long ak[GEN ? A_INS : 1], ao[GEN ? A_INS : 1], ak2[GEN ? A_INS : 1], last[GEN ? A_INS : 1];
+  const long long q8 = 8 / p.K2, r8 = 8 - q8 * p.K2, step = q8 * sK1 + r8;
+  if constexpr (GEN) {
 #pragma unroll
-    for (int it = 0; it < A_INS; ++it)
-      __builtin_amdgcn_global_load_lds((const void*)(abase + src_off(it, a_rs)), PSIM_LDS(sa + (it * 4 + wid) * (1024 / (int)sizeof(T))),
-                                       16, 0, 0);
+    for (int it = 0; it < A_INS; ++it) {
+      const int c = chunk_of(it);
+      const long long m = min(m0 + row_of(it), p.M - 1);
+      const long long k1 = c / p.K2;
+      ak[it] = c;
+      ak2[it] = c - k1 * p.K2;
+      ao[it] = k1 * sK1 + m * p.K2 + ak2[it];
+      last[it] = (p.K1 - 1) * sK1 + m * p.K2 + p.K2 - 1;
+    }
+  }
+  auto issue = [&](double* sa, double* sb) {
+    if constexpr (GEN) {
 #pragma unroll
-    for (int it = 0; it < B_INS; ++it)
-      __builtin_amdgcn_global_load_lds((const void*)(bbase + src_off(it, b_rs)), PSIM_LDS(sb + (it * 4 + wid) * (1024 / (int)sizeof(T))),
-                                       16, 0, 0);
-    fk2 += BK / 2;
-    if (fk2 == p.K2) {
-      fk2 = 0;
-      ++fk1;
+      for (int it = 0; it < A_INS; ++it) {
+        const double* src = A + 2 * (ak[it] < p.K ? ao[it] : last[it]);
+        __builtin_amdgcn_global_load_lds((const void*)src, PSIM_LDS(sa + (it * 4 + wid) * 128), 16, 0, 0);
+        ak[it] += 8;
+        ak2[it] += r8;
+        ao[it] += step;
+        if (ak2[it] >= p.K2) {
+          ak2[it] -= p.K2;
+          ao[it] += sK1 - p.K2;
+        }
+      }
+#pragma unroll
+      for (int it = 0; it < B_INS; ++it) {
+        const double* src = W + (n0 + row_of(it)) * p.ldw + kr + 2 * chunk_of(it);
+        __builtin_amdgcn_global_load_lds((const void*)src, PSIM_LDS(sb + (it * 4 + wid) * 128), 16, 0, 0);
+      }
+    } else {
+      const char* abase = (const char*)(A + 2 * (fk1 * sK1 + m0 * p.K2 + fk2));
+      const char* bbase = (const char*)(W + n0 * p.ldw + kr);
+#pragma unroll
+      for (int it = 0; it < A_INS; ++it)
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(abase + ((unsigned)row_of(it) * a_rs + (unsigned)chunk_of(it) * 16u)),
+            PSIM_LDS(sa + (it * 4 + wid) * 128), 16, 0, 0);
+#pragma unroll
+      for (int it = 0; it < B_INS; ++it)
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(bbase + ((unsigned)row_of(it) * b_rs + (unsigned)chunk_of(it) * 16u)),
+            PSIM_LDS(sb + (it * 4 + wid) * 128), 16, 0, 0);
+      fk2 += BK / 2;
+      if (fk2 == p.K2) {
+        fk2 = 0;
+        ++fk1;
+      }
     }
     kr += BK;
   };
@@ -665,46 +708,57 @@ __global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
 #pragma unroll
       for (int r = 0; r < MF::NACC; ++r) acc[bi][bj][r] = 0;
 
-  const int frow = lane % MF::MB;
-  const int fq = lane / MF::MB;  // which chunk of a group of 8 k this lane reads
-  auto compute = [&](const T* a_s, const T* b_s) {
+  const int frow = lane & 15;
+  const int fq = lane >> 4;  // which chunk of a group of 4 this lane reads
+  // left: complex k of the stage that count (GEN)
+  auto compute = [&](const double* a_s, const double* b_s, const int left) {
 #pragma unroll
     for (int g = 0; g < BK / 8; ++g) {
-      typename MF::frag_t af[MBLK], bf[NBLK];
+      if (GEN && 4 * g >= left) break;
+      f64x2 af[MBLK], bf[NBLK];
 #pragma unroll
       for (int bi = 0; bi < MBLK; ++bi) {
-        const int r = wr * WM + bi * MF::MB + frow;
-        af[bi] = *(const typename MF::frag_t*)(a_s + r * BK + (((g * (8 / KV) + fq) ^ dtl_swz(r)) * KV));
+        const int r = wr * WM + bi * 16 + frow;
+        af[bi] = *(const f64x2*)(a_s + r * BK + (((g * 4 + fq) ^ dtl_swz(r)) * 2));
+        if (GEN && 4 * g + fq >= left) af[bi] = f64x2{0, 0};
       }
 #pragma unroll
       for (int bj = 0; bj < NBLK; ++bj) {
-        const int r = wc * WN + bj * MF::MB + frow;
-        bf[bj] = *(const typename MF::frag_t*)(b_s + r * BK + (((g * (8 / KV) + fq) ^ dtl_swz(r)) * KV));
+        const int r = wc * WN + bj * 16 + frow;
+        bf[bj] = *(const f64x2*)(b_s + r * BK + (((g * 4 + fq) ^ dtl_swz(r)) * 2));
       }
 #pragma unroll
-      for (int s = 0; s < MF::KV; ++s)
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int bi = 0; bi < MBLK; ++bi)
 #pragma unroll
-          for (int bj = 0; bj < NBLK; ++bj) MF::mma(af[bi], bf[bj], acc[bi][bj], s);
+          for (int bj = 0; bj < NBLK; ++bj) {
+            if (TRANS)
+              MF::mma(bf[bj], af[bi], acc[bi][bj], s);
+            else
+              MF::mma(af[bi], bf[bj], acc[bi][bj], s);
+          }
     }
   };
   constexpr unsigned kWaitVm0 = 0x3f70;
 
-  const int npair = (int)(p.Kr / (2 * BK));
+  const int nst = (int)((p.K + 7) / 8);
+  const int klast = (int)(p.K - 8LL * (nst - 1));
   issue(sA0, sB0);
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
   __syncthreads();
-  for (int kp = 0; kp < npair; ++kp) {
+  int st = 0;
+  for (; st + 1 < nst; st += 2) {
     issue(sA1, sB1);
-    compute(sA0, sB0);
+    compute(sA0, sB0, 8);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
-    if (kp + 1 < npair) issue(sA0, sB0);
-    compute(sA1, sB1);
+    if (st + 2 < nst) issue(sA0, sB0);
+    compute(sA1, sB1, st + 2 < nst ? 8 : klast);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
   }
+  if (GEN && st < nst) compute(sA0, sB0, klast);
 
 #pragma unroll
   for (int bi = 0; bi < MBLK; ++bi)
@@ -712,9 +766,20 @@ __global__ __launch_bounds__(256, OCC) void site_gemm_4m_dtl(KArgs p) {
     for (int bj = 0; bj < NBLK; ++bj)
 #pragma unroll
       for (int r = 0; r < MF::NACC; ++r) {
-        const long long row = m0 + wr * WM + bi * MF::MB + MF::out_row(lane, r);
-        const long long col = n0 + wc * WN + bj * MF::MB + MF::out_col(lane);
-        if (col < p.Nr) C[row * p.Nr + col] = acc[bi][bj][r];
+        const int br = MF::out_row(lane, r), bc = MF::out_col(lane);
+        const long long row = m0 + wr * WM + bi * 16 + (TRANS ? bc : br);
+        const long long col = n0 + wc * WN + bj * 16 + (TRANS ? br : bc);
+        if ((GEN && row >= p.M) || col >= p.Nr) continue;
+        const double v = acc[bi][bj][r];
+        if constexpr (TRANS) {
+          double* dst = C + 2 * ((col >> 1) * p.ldct + row) + (col & 1);
+          *dst = p.beta ? *dst + v : v;
+        } else if (GEN && p.nb) {
+          const long long cc = col >> 1;
+          C[2 * ((cc / p.nb) * p.sCw + row * p.nb + cc % p.nb) + (col & 1)] = v;
+        } else {
+          C[row * p.Nr + col] = v;
+        }
       }
 }
 
@@ -1144,8 +1209,7 @@ int fp32_config_count() { return (int)(sizeof(kFp32Configs) / sizeof(kFp32Config
 // the half-precision units (site_f16.hip).
 static const FCfg kFp32_3mConfigs[] = {{128, 128, 32}, {256, 128, 32}, {128, 256, 32}, {64, 128, 32}};
 int fp32_3m_config_count() { return (int)(sizeof(kFp32_3mConfigs) / sizeof(kFp32_3mConfigs[0])); }
-// FP64 candidates: 0 = direct-to-LDS 128 x 64, 1 = direct-to-LDS 64 x 64,
-// 2 = row-major 128 x 64 x 16 (LDS through registers)
+// FP64 candidates: 0 = 128 x 64 tiles, 1 = 64 x 64, 2 = as 0
 int fp64_config_count() { return 3; }
 // BF16x3 candidates: 0 = 256 x 256 tiles, 1 = 128 x 256, 2 = as 0 (for the
 // shapes that do not go to site_f16.hip)
@@ -1308,51 +1372,31 @@ void launch_site_gemm(const GemmLaunch& g, void* stream) {
   // batch entries = nodes * Bz; the kernel splits z = node * Bz + v
   const long long Z = g.nodes * g.Bz;
   if (g.prec == PSIM_FP64) {
-    KArgs b = a;
-    b.MT = (b.M + 64 - 1) / 64;
-    b.NT = (b.Nr + 64 - 1) / 64;
-    b.T = b.MT * b.NT * Z;
-    const long long blocks = (b.T + 7) / 8 * 8;
+    // every stage inside one k1 block, an even number of them, 128-row tiles
+    // interior, 32-bit copy offsets: 128 x 64 tiles (candidate 1: 64 x 64);
+    // transposed stores of few columns (last sites) take 128 x 32 (5x5 (1+32+1):
+    // 11.4 ms against 15.8 in 64 x 64 tiles), every other launch 64 x 64 (a plain
+    // store of 16 columns loses in 128 x 32: 54 against 50 us)
+    const bool hot = !g.trans_out && !g.nb && g.K2 % 8 == 0 && g.M % 128 == 0 && (g.K1 * g.K2) % 16 == 0 &&
+                     g.K2 < (1 << 20) && g.ldw < (1 << 22);
+    const bool narrow = g.trans_out && g.N <= 16;
+    const int bm = (hot && g.cfg != 1) || narrow ? 128 : 64, bn = narrow ? 32 : 64;
+    a.MT = (a.M + bm - 1) / bm;
+    a.NT = (a.Nr + bn - 1) / bn;
+    a.T = a.MT * a.NT * Z;
+    const long long blocks = (a.T + 7) / 8 * 8;
     if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-    const bool kmajor = g.K2 == 1 && g.K1 > 1;
-    // interior-only row-major launches (every stage inside one k1 block):
-    // 128 x 64 tiles with the division-free loader
-    const bool fastd = !g.trans_out && !g.nb && g.K2 % 8 == 0 && g.M % 128 == 0;
-    const bool dtl_ok = fastd && (g.K1 * g.K2) % 16 == 0 && g.K2 < (1 << 20) && g.ldw < (1 << 22);
-    if (dtl_ok && g.cfg == 1) {
-      // candidate 1: 64 x 64 tiles
-      KArgs f = a;
-      f.MT = f.M / 64;
-      f.NT = (f.Nr + 64 - 1) / 64;
-      f.T = f.MT * f.NT * Z;
-      const long long fb = (f.T + 7) / 8 * 8;
-      if (fb > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-      hipLaunchKernelGGL((site_gemm_4m_dtl<double, 64, 64, 4>), dim3((unsigned)fb), dim3(256), 0, st, f);
-    } else if (dtl_ok && g.cfg != 2) {
-      // an even number of 16-double stages, 32-bit copy offsets: direct-to-LDS
-      KArgs f = a;
-      f.MT = f.M / 128;
-      f.NT = (f.Nr + 64 - 1) / 64;
-      f.T = f.MT * f.NT * Z;
-      const long long fb = (f.T + 7) / 8 * 8;
-      if (fb > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-      hipLaunchKernelGGL((site_gemm_4m_dtl<double, 128, 64, 3>), dim3((unsigned)fb), dim3(256), 0, st, f);
-    } else if (fastd) {
-      KArgs f = a;
-      f.MT = f.M / 128;
-      f.NT = (f.Nr + 64 - 1) / 64;
-      f.T = f.MT * f.NT * Z;
-      const long long fb = (f.T + 7) / 8 * 8;
-      if (fb > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
-      launch<double, 128, 64, 16, ROWFAST, false>(f, fb, st);
-    } else if (kmajor && g.trans_out)
-      launch<double, 64, 64, 16, KMAJOR, true>(b, blocks, st);
-    else if (kmajor)
-      launch<double, 64, 64, 16, KMAJOR, false>(b, blocks, st);
+    const dim3 grid((unsigned)blocks), wg(256);
+    if (hot && g.cfg == 1)
+      hipLaunchKernelGGL((site_gemm_f64<64, 64, 4, false, false>), grid, wg, 0, st, a);
+    else if (hot)
+      hipLaunchKernelGGL((site_gemm_f64<128, 64, 3, false, false>), grid, wg, 0, st, a);
+    else if (narrow)
+      hipLaunchKernelGGL((site_gemm_f64<128, 32, 3, true, true>), grid, wg, 0, st, a);
     else if (g.trans_out)
-      launch<double, 64, 64, 16, GENERIC, true>(b, blocks, st);
+      hipLaunchKernelGGL((site_gemm_f64<64, 64, 4, true, true>), grid, wg, 0, st, a);
     else
-      launch<double, 64, 64, 16, GENERIC, false>(b, blocks, st);
+      hipLaunchKernelGGL((site_gemm_f64<64, 64, 4, true, false>), grid, wg, 0, st, a);
   } else {
     KArgs b = a;
     b.MT = (b.M + 128 - 1) / 128;
