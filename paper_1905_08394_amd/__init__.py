@@ -276,6 +276,7 @@ class Plan:
         self.device = device
         self.nq = peps.lv * peps.lh
         self._ws = None
+        self._need = None  # workspace bytes, fixed by the plan
 
     def stats(self) -> dict:
         s = PlanStats()
@@ -284,10 +285,11 @@ class Plan:
 
     def workspace(self):
         import torch
-        need = self.stats()["workspace_bytes"]
-        if self._ws is None or self._ws.numel() < need:
+        if self._need is None:
+            self._need = self.stats()["workspace_bytes"]
+        if self._ws is None or self._ws.numel() < self._need:
             self._ws = None
-            self._ws = torch.empty(need, dtype=torch.uint8, device=f"cuda:{self.device}")
+            self._ws = torch.empty(self._need, dtype=torch.uint8, device=f"cuda:{self.device}")
         return self._ws
 
     def amplitudes(self, bits, stream=None, rel_err: bool = False):
@@ -382,11 +384,12 @@ class Group:
         wss = [p.workspace() for p in self.plans]
         PU8 = ctypes.POINTER(ctypes.c_uint8)
         PD = ctypes.POINTER(ctypes.c_double)
-        c_bits = (PU8 * np_)(*[b.ctypes.data_as(PU8) for b in bs])
+        vps = ctypes.c_void_p * np_
+        c_bits = ctypes.cast(vps(*[b.ctypes.data for b in bs]), ctypes.POINTER(PU8))
         c_n = (ctypes.c_size_t * np_)(*[b.shape[0] for b in bs])
-        c_ws = (ctypes.c_void_p * np_)(*[w.data_ptr() for w in wss])
+        c_ws = vps(*[w.data_ptr() for w in wss])
         c_wsb = (ctypes.c_size_t * np_)(*[w.numel() for w in wss])
-        c_out = (PD * np_)(*[o.ctypes.data_as(PD) for o in outs])
+        c_out = ctypes.cast(vps(*[o.ctypes.data for o in outs]), ctypes.POINTER(PD))
         dev = self.plans[0].device
         st = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
         _check(lib().psim_group_amplitudes(self._h, c_bits, c_n, c_ws, c_wsb, ctypes.c_void_p(st), c_out))

@@ -17,7 +17,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <unordered_map>
+#include <mutex>
 
 #include <hip/hip_runtime_api.h>
 
@@ -34,33 +34,44 @@ struct Trie {
   std::vector<int32_t> leaf;              // per bitstring: node at the last level
 };
 
-Trie build_trie(const psim_plan_t& pl, const uint8_t* bits, size_t n) {
+// Bits of every bitstring's swept rows: key[b * R + i] holds row i's, bit j =
+// column j.
+std::vector<uint64_t> row_keys(const psim_plan_t& pl, const uint8_t* bits, size_t n) {
   const int R = pl.R, L = pl.L, nq = pl.lv * pl.lh;
+  std::vector<uint64_t> key(n * R);
+  for (size_t b = 0; b < n; ++b)
+    for (int i = 0; i < R; ++i) {
+      uint64_t k = 0;
+      for (int j = 0; j < L; ++j) k |= (uint64_t)bits[b * nq + pl.cs[(size_t)i * L + j].qubit] << j;
+      key[b * R + i] = k;
+    }
+  return key;
+}
+
+// First row where two bitstrings differ (R: nowhere).
+int first_difference(const uint64_t* x, const uint64_t* y, int R) {
+  int i = 0;
+  while (i < R && x[i] == y[i]) ++i;
+  return i;
+}
+
+// Trie of the bitstrings idx, which are sorted by their rows: every prefix is a
+// run of them, so a bitstring opens a node at each level from the first row where
+// it leaves the one before.
+Trie build_trie(const psim_plan_t& pl, const std::vector<uint64_t>& key, const std::vector<size_t>& idx) {
+  const int R = pl.R, L = pl.L;
   Trie t;
   t.parent.resize(R);
   t.tau.resize(R);
-  std::vector<int32_t> cur(n, 0);  // node of each bitstring at the previous level (root = 0)
-  for (int i = 0; i < R; ++i) {
-    std::map<std::pair<int32_t, uint64_t>, int32_t> index;
-    std::vector<int32_t> next(n);
-    for (size_t b = 0; b < n; ++b) {
-      uint64_t key = 0;
-      for (int j = 0; j < L; ++j) key |= (uint64_t)bits[b * nq + pl.cs[(size_t)i * L + j].qubit] << j;
-      auto k = std::make_pair(cur[b], key);
-      auto it = index.find(k);
-      if (it == index.end()) {
-        const int32_t id = (int32_t)t.parent[i].size();
-        index.emplace(k, id);
-        t.parent[i].push_back(cur[b]);
-        for (int j = 0; j < L; ++j) t.tau[i].push_back((uint8_t)((key >> j) & 1));
-        next[b] = id;
-      } else {
-        next[b] = it->second;
-      }
+  t.leaf.resize(idx.size());
+  for (size_t x = 0; x < idx.size(); ++x) {
+    const uint64_t* k = &key[idx[x] * R];
+    for (int i = x ? first_difference(&key[idx[x - 1] * R], k, R) : 0; i < R; ++i) {
+      t.parent[i].push_back(i ? (int32_t)t.parent[i - 1].size() - 1 : 0);
+      for (int j = 0; j < L; ++j) t.tau[i].push_back((uint8_t)((k[i] >> j) & 1));
     }
-    cur.swap(next);
+    t.leaf[x] = (int32_t)t.parent[R - 1].size() - 1;
   }
-  t.leaf = cur;
   return t;
 }
 
@@ -227,40 +238,28 @@ void check_batch(const psim_plan_t* pl, const uint8_t* bits, size_t n, void* ws,
 // Sub-batches whose prefix trie fits the planned capacities: sort the
 // bitstrings by their swept rows (row 0 first) so that neighbours share the
 // longest prefixes, then cut greedily.  Returns lists of bitstring indices.
-std::vector<std::vector<size_t>> split_batches(const psim_plan_t* pl, const uint8_t* bits, size_t n) {
-  const int nq = pl->lv * pl->lh;
+std::vector<std::vector<size_t>> split_batches(const psim_plan_t* pl, const std::vector<uint64_t>& key, size_t n) {
+  const int R = pl->R;
   std::vector<size_t> order(n);
   for (size_t b = 0; b < n; ++b) order[b] = b;
-  auto rowkey = [&](size_t b, int i) {
-    uint64_t key = 0;
-    for (int j = 0; j < pl->L; ++j) key |= (uint64_t)bits[b * nq + pl->cs[(size_t)i * pl->L + j].qubit] << j;
-    return key;
-  };
   std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
-    for (int i = 0; i < pl->R; ++i) {
-      const uint64_t a = rowkey(x, i), b = rowkey(y, i);
-      if (a != b) return a < b;
-    }
-    return false;
+    return std::lexicographical_compare(&key[x * R], &key[x * R] + R, &key[y * R], &key[y * R] + R);
   });
   std::vector<std::vector<size_t>> out;
-  std::vector<int64_t> count(pl->R, 0);
+  std::vector<int64_t> count(R, 0);
   size_t start = 0;
   for (size_t x = 0; x < n; ++x) {
     // first swept row where this bitstring leaves the previous one's path
-    int first = 0;
-    if (x > start) {
-      while (first < pl->R && rowkey(order[x], first) == rowkey(order[x - 1], first)) ++first;
-    }
+    int first = x > start ? first_difference(&key[order[x - 1] * R], &key[order[x] * R], R) : 0;
     bool fits = (int64_t)(x - start + 1) <= (int64_t)pl->opts.max_batch;
-    for (int i = (x > start ? first : 0); i < pl->R && fits; ++i) fits = count[i] + 1 <= pl->levels[i].cap;
+    for (int i = first; i < R && fits; ++i) fits = count[i] + 1 <= pl->levels[i].cap;
     if (!fits) {
       out.emplace_back(order.begin() + start, order.begin() + x);
       start = x;
       std::fill(count.begin(), count.end(), 0);
       first = 0;
     }
-    for (int i = (x > start ? first : 0); i < pl->R; ++i) ++count[i];
+    for (int i = first; i < R; ++i) ++count[i];
   }
   if (n > start) out.emplace_back(order.begin() + start, order.end());
   return out;
@@ -290,28 +289,26 @@ struct Op {
 // workspace) and the ordered operations that contract it.
 struct Prepared {
   psim_plan_t* pl = nullptr;
-  std::vector<uint8_t> bits;  // the sub-batch's bitstrings, nq bytes each
   size_t n = 0;
   Trie t;
   WsLayout W;
   std::vector<Op> ops;
-  std::vector<char> vals;     // downloaded leaf boundaries (scalars)
-  std::vector<int32_t> ex;    // and their exponents
+  std::vector<char> buf;      // results, where no staging buffer holds them
+  const char* vals = nullptr;  // downloaded leaf boundaries (scalars)
+  const int32_t* ex = nullptr;  // and their exponents
 };
 
 // Builds the trie and the operation list of one sub-batch.  The trie tables
 // and the root exponent are written to tab_img, the host image of the table
 // region (pl->ws_tab bytes, zero-filled by the caller); the caller uploads it
 // to P.W.tab before the operations run.
-void prepare(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& idx, void* ws, char* tab_dev,
-             char* tab_img, Prepared& P) {
-  const int R = pl->R, L = pl->L, prec = pl->opts.prec, nq = pl->lv * pl->lh;
+void prepare(psim_plan_t* pl, const std::vector<uint64_t>& key, const std::vector<size_t>& idx, void* ws,
+             char* tab_dev, char* tab_img, Prepared& P) {
+  const int R = pl->R, L = pl->L, prec = pl->opts.prec;
   const uint64_t eb = pl->elem_bytes;
   P.pl = pl;
   P.n = idx.size();
-  P.bits.resize(P.n * nq);
-  for (size_t x = 0; x < P.n; ++x) std::memcpy(&P.bits[x * nq], bits + idx[x] * nq, nq);
-  P.t = build_trie(*pl, P.bits.data(), P.n);
+  P.t = build_trie(*pl, key, idx);
   P.W = layout(*pl, ws, tab_dev);
   const Trie& t = P.t;
   WsLayout& W = P.W;
@@ -558,39 +555,84 @@ void run_op(const psim_plan_t* pl, const Op& op, hipStream_t st) {
     launch_site_gemm(op.g, st);
 }
 
-void enqueue_download(Prepared& P, hipStream_t st) {
+// Pinned host memory of one call: the image of the trie tables (ws_tab bytes),
+// then the leaf values and exponents, which a kernel writes there itself.  A
+// plan keeps the buffers of finished calls, so there are as many as calls have
+// overlapped; calls without one (static workspace, more than kMaxStaging bytes,
+// or none to be had) use pageable memory.
+constexpr uint64_t kMaxStaging = 4 << 20;
+struct Staging {
+  psim_plan_t* pl;
+  char* h = nullptr;
+  Staging(psim_plan_t* p, bool want) : pl(p) {
+    if (!want) return;
+    {
+      std::lock_guard<std::mutex> lk(pl->staging_mu);
+      if (!pl->staging.empty()) {
+        h = (char*)pl->staging.back();
+        pl->staging.pop_back();
+        return;
+      }
+    }
+    const uint64_t bytes = pl->ws_tab + (uint64_t)pl->levels[pl->R - 1].cap * (pl->elem_bytes + 4);
+    if (bytes > kMaxStaging) return;
+    {
+      std::lock_guard<std::mutex> lk(pl->staging_mu);
+      pl->staging.reserve(++pl->staging_made);  // giving it back allocates nothing
+    }
+    if (hipHostMalloc((void**)&h, bytes, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      h = nullptr;
+    }
+  }
+  ~Staging() {
+    if (!h) return;
+    std::lock_guard<std::mutex> lk(pl->staging_mu);
+    pl->staging.push_back(h);
+  }
+  Staging(const Staging&) = delete;
+  Staging& operator=(const Staging&) = delete;
+};
+
+void enqueue_download(Prepared& P, const Staging& sg, hipStream_t st) {
   const psim_plan_t* pl = P.pl;
   const int R = pl->R;
-  const int64_t leaves = (int64_t)P.t.parent[R - 1].size();
-  P.vals.resize((size_t)leaves * pl->elem_bytes);
-  P.ex.resize((size_t)leaves);
-  hip_check(hipMemcpyAsync(P.vals.data(), P.W.F[(R - 1) % 2], P.vals.size(), hipMemcpyDeviceToHost, st), "download");
-  hip_check(hipMemcpyAsync(P.ex.data(), P.W.exp[(R - 1) % 2], P.ex.size() * 4, hipMemcpyDeviceToHost, st),
-            "download");
+  const size_t leaves = P.t.parent[R - 1].size(), vb = leaves * pl->elem_bytes;
+  const char* F = P.W.F[(R - 1) % 2];
+  const int32_t* ex = P.W.exp[(R - 1) % 2];
+  if (sg.h) {
+    char* dst = sg.h + pl->ws_tab;
+    launch_copy_pair(F, dst, (int64_t)vb, ex, dst + vb, (int64_t)leaves * 4, st);
+    P.vals = dst;
+    P.ex = (const int32_t*)(dst + vb);
+    return;
+  }
+  P.buf.resize(vb + leaves * 4);
+  hip_check(hipMemcpyAsync(P.buf.data(), F, vb, hipMemcpyDeviceToHost, st), "download");
+  hip_check(hipMemcpyAsync(P.buf.data() + vb, ex, leaves * 4, hipMemcpyDeviceToHost, st), "download");
+  P.vals = P.buf.data();
+  P.ex = (const int32_t*)(P.buf.data() + vb);
 }
 
 // amplitude b = mantissa * 2^(row exponents + site-matrix exponents), in FP64
-void assemble(const Prepared& P, const std::vector<size_t>& idx, double* out) {
+void assemble(const Prepared& P, const uint8_t* bits, const std::vector<size_t>& idx, double* out) {
   const psim_plan_t* pl = P.pl;
-  const int R = pl->R, L = pl->L, nq = pl->lv * pl->lh;
+  const int nq = pl->lv * pl->lh;
   for (size_t b = 0; b < P.n; ++b) {
     const int32_t leaf = P.t.leaf[b];
     double re, im;
     if (pl->elem_bytes == 16) {
-      const double* v = (const double*)P.vals.data();
+      const double* v = (const double*)P.vals;
       re = v[2 * leaf];
       im = v[2 * leaf + 1];
     } else {
-      const float* v = (const float*)P.vals.data();
+      const float* v = (const float*)P.vals;
       re = v[2 * leaf];
       im = v[2 * leaf + 1];
     }
     int64_t e = P.ex[leaf];
-    for (int i = 0; i < R; ++i)
-      for (int j = 0; j < L; ++j) {
-        const int tau = P.bits[b * nq + pl->cs[(size_t)i * L + j].qubit];
-        e += pl->w[((size_t)i * L + j) * 2 + tau].exp2;
-      }
+    const uint8_t* t = bits + idx[b] * nq;
+    for (int q = 0; q < nq; ++q) e += pl->qubit_exp[2 * q + t[q]];
     out[2 * idx[b]] = std::ldexp(re, (int)e);
     out[2 * idx[b] + 1] = std::ldexp(im, (int)e);
   }
@@ -598,12 +640,23 @@ void assemble(const Prepared& P, const std::vector<size_t>& idx, double* out) {
 
 // One sub-batch of one plan on its own: optional event timing, row progress
 // log, or graph capture / replay of the operation list.
-void run_one(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& idx, void* ws, hipStream_t st,
-             double* out, bool no_alloc) {
+void run_one(psim_plan_t* pl, const uint8_t* bits, const std::vector<uint64_t>& key, const std::vector<size_t>& idx,
+             void* ws, hipStream_t st, double* out, bool no_alloc) {
   Prepared P;
-  std::vector<char> img(pl->ws_tab, 0);
-  prepare(pl, bits, idx, ws, nullptr, img.data(), P);
-  hip_check(hipMemcpyAsync(P.W.tab, img.data(), img.size(), hipMemcpyHostToDevice, st), "upload tables");
+  const Staging sg(pl, !no_alloc);
+  std::vector<char> pageable(sg.h ? 0 : pl->ws_tab);
+  char* img = sg.h ? sg.h : pageable.data();
+  std::memset(img, 0, pl->ws_tab);
+  prepare(pl, key, idx, ws, nullptr, img, P);
+  // the buffer goes back only after the stream has been waited for, also on an error
+  struct Wait {
+    hipStream_t st;
+    bool pending;
+    ~Wait() {
+      if (pending) (void)hipStreamSynchronize(st);
+    }
+  } wait{st, true};
+  hip_check(hipMemcpyAsync(P.W.tab, img, pl->ws_tab, hipMemcpyHostToDevice, st), "upload tables");
 
   struct Timed {
     hipEvent_t a, b;
@@ -686,8 +739,9 @@ void run_one(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
   }
   if (gexec) hip_check(hipGraphLaunch(gexec, st), "hipGraphLaunch");
 
-  enqueue_download(P, st);
+  enqueue_download(P, sg, st);
   hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
+  wait.pending = false;
   for (Timed& tm : timed) {
     float ms = 0;
     hip_check(hipEventElapsedTime(&ms, tm.a, tm.b), "hipEventElapsedTime");
@@ -698,7 +752,7 @@ void run_one(psim_plan_t* pl, const uint8_t* bits, const std::vector<size_t>& id
     (void)hipEventDestroy(tm.a);
     (void)hipEventDestroy(tm.b);
   }
-  assemble(P, idx, out);
+  assemble(P, bits, idx, out);
 }
 
 }  // namespace
@@ -710,7 +764,9 @@ void sweep(psim_plan_t* pl, const uint8_t* bits, size_t n, void* ws, void* strea
     run_square(pl, bits, n, ws, stream, res, no_alloc);
   } else {
     hip_check(hipSetDevice(pl->opts.device), "hipSetDevice");
-    for (const auto& idx : split_batches(pl, bits, n)) run_one(pl, bits, idx, ws, (hipStream_t)stream, res, no_alloc);
+    const std::vector<uint64_t> key = row_keys(*pl, bits, n);
+    for (const auto& idx : split_batches(pl, key, n))
+      run_one(pl, bits, key, idx, ws, (hipStream_t)stream, res, no_alloc);
   }
 }
 
@@ -834,9 +890,13 @@ void run_group(psim_group_s* G, const uint8_t* const* bits, const size_t* n, voi
   hip_check(hipSetDevice(G->device), "hipSetDevice");
   hipStream_t st = (hipStream_t)stream;
   std::vector<std::vector<std::vector<size_t>>> subs(np);
+  std::vector<std::vector<uint64_t>> keys(np);
   size_t passes = 0;
   for (int p = 0; p < np; ++p) {
-    if (n[p]) subs[p] = split_batches(G->plans[p], bits[p], n[p]);
+    if (n[p]) {
+      keys[p] = row_keys(*G->plans[p], bits[p], n[p]);
+      subs[p] = split_batches(G->plans[p], keys[p], n[p]);
+    }
     passes = std::max(passes, subs[p].size());
   }
   const int kb = kargs_bytes();
@@ -858,7 +918,7 @@ void run_group(psim_group_s* G, const uint8_t* const* bits, const size_t* n, voi
         P.emplace_back();
         who.push_back(p);
         std::memset(hbuf + G->tab_off[p], 0, G->plans[p]->ws_tab);
-        prepare(G->plans[p], bits[p], subs[p][pass], ws[p], dbuf + G->tab_off[p], hbuf + G->tab_off[p], P.back());
+        prepare(G->plans[p], keys[p], subs[p][pass], ws[p], dbuf + G->tab_off[p], hbuf + G->tab_off[p], P.back());
       }
     const size_t m = P.size();
     std::vector<std::vector<int>> variant(m);
@@ -992,12 +1052,9 @@ void run_group(psim_group_s* G, const uint8_t* const* bits, const size_t* n, voi
     hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
     for (size_t q = 0; q < m; ++q) {
       const int p = who[q];
-      const psim_plan_t* pl = P[q].pl;
-      const size_t leaves = P[q].t.parent[pl->R - 1].size();
-      P[q].vals.assign(hbuf + G->res_off[p], hbuf + G->res_off[p] + leaves * pl->elem_bytes);
-      P[q].ex.resize(leaves);
-      std::memcpy(P[q].ex.data(), hbuf + G->res_exp_off[p], leaves * 4);
-      assemble(P[q], subs[who[q]][pass], res[who[q]].data());
+      P[q].vals = hbuf + G->res_off[p];
+      P[q].ex = (const int32_t*)(hbuf + G->res_exp_off[p]);
+      assemble(P[q], bits[p], subs[p][pass], res[p].data());
     }
   }
   for (int p = 0; p < np; ++p)

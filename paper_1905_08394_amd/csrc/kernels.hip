@@ -1060,6 +1060,19 @@ __global__ void copy_segments(const CopySeg* __restrict__ segs) {
     b[x] = a[x];
 }
 
+// Results of a call (4-byte words) into the caller's pinned memory: one launch
+// in place of two downloads that each wait for the host.
+__global__ void copy_pair(const uint32_t* __restrict__ a, uint32_t* __restrict__ to_a, long long na,
+                          const uint32_t* __restrict__ b, uint32_t* __restrict__ to_b, long long nb) {
+  for (long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x; x < na + nb;
+       x += (long long)gridDim.x * blockDim.x) {
+    if (x < na)
+      to_a[x] = a[x];
+    else
+      to_b[x - na] = b[x - na];
+  }
+}
+
 // ---------------------------------------------------------------- square partition helpers
 // Three-index permutes of a complex tensor in[X][Y][Z] (E = float2 or
 // double2, one complex element): mode 0 writes out[Y][X][Z], mode 1
@@ -1602,6 +1615,15 @@ void launch_copy_segments(const CopySeg* d_segs, int n, int64_t max_bytes, void*
   const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_bytes + 255) / 256, 64));
   hipLaunchKernelGGL(copy_segments, dim3(gx, (unsigned)n), dim3(256), 0, (hipStream_t)stream, d_segs);
   hip_check(hipGetLastError(), "gather launch");
+}
+
+void launch_copy_pair(const void* a, void* to_a, int64_t bytes_a, const void* b, void* to_b, int64_t bytes_b,
+                      void* stream) {
+  const int64_t words = (bytes_a + bytes_b) / 4;
+  const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>((words + 255) / 256, 256));
+  hipLaunchKernelGGL(copy_pair, dim3(gx), dim3(256), 0, (hipStream_t)stream, (const uint32_t*)a, (uint32_t*)to_a,
+                     (long long)(bytes_a / 4), (const uint32_t*)b, (uint32_t*)to_b, (long long)(bytes_b / 4));
+  hip_check(hipGetLastError(), "result copy launch");
 }
 
 bool rescale_fusable(int64_t per_node) { return 2 * per_node <= kFusedScaleReals; }

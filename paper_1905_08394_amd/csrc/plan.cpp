@@ -553,6 +553,9 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
           }
         }
       }
+    pl->qubit_exp.resize((size_t)2 * R * L);
+    for (size_t x = 0; x < pl->cs.size(); ++x)
+      for (int tau = 0; tau < 2; ++tau) pl->qubit_exp[2 * pl->cs[x].qubit + tau] = pl->w[2 * x + tau].exp2;
     if (!pl->host_only) {
       hip_check(hipMalloc(&pl->d_ones, 16), "hipMalloc(ones)");
       launch_fill_ones(opts.prec, pl->d_ones, nullptr);
@@ -574,6 +577,7 @@ void free_plan(psim_plan_t* pl) {
   if (!pl) return;
   for (auto& kv : pl->graphs) (void)hipGraphExecDestroy((hipGraphExec_t)kv.second);
   if (pl->cap_stream) (void)hipStreamDestroy((hipStream_t)pl->cap_stream);
+  for (void* h : pl->staging) (void)hipHostFree(h);
   for (auto& dm : pl->w) {
     if (dm.ptr) (void)hipFree(dm.ptr);
     if (dm.ptr_b) (void)hipFree(dm.ptr_b);

@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -109,6 +110,10 @@ struct psim_plan_s {
   std::vector<psim::Level> levels;       // R
   std::vector<psim::Step> steps;         // per row i: L steps (index i * L + j)
   std::vector<psim::DevMatrix> w;        // per site and tau: (i * L + j) * 2 + tau
+  std::vector<int32_t> qubit_exp;        // row scheme: exponent of qubit q's site matrix for value t at 2 q + t
+  std::vector<void*> staging;            // pinned host buffers not in use (exec.cpp), guarded by staging_mu
+  size_t staging_made = 0;
+  std::mutex staging_mu;
   double cmac = 0;
   int64_t peak_elems = 0;
   uint64_t weights_bytes = 0;
@@ -295,6 +300,9 @@ struct CopySeg {
   int64_t bytes;
 };
 void launch_copy_segments(const CopySeg* d_segs, int n, int64_t max_bytes, void* stream);
+// two small copies in one launch; the destinations may be pinned host memory
+void launch_copy_pair(const void* a, void* to_a, int64_t bytes_a, const void* b, void* to_b, int64_t bytes_b,
+                      void* stream);
 // square partition: complex in[X][Y][Z] -> out[Y][X][Z] (mode 0) or out[X][Z][Y]
 // (mode 1), for `nodes` tensors X*Y*Z elements apart
 // (mx, nullable: per-node exponent + 4096 from launch_row_exponents; the
