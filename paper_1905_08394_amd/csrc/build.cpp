@@ -258,8 +258,16 @@ psim_peps_t* build_peps(int32_t lv, int32_t lh, const psim_gate* gates, size_t n
 
 // More gates on an existing state (the remark after eq. 7: gates may follow
 // a measurement); applied to a copy, so a failing gate leaves P unchanged.
+// A doubled site as a plain tensor, before it is changed.
+static void hold_tensor(Site& s) {
+  if (!s.layer) return;
+  s.t = host_tensor(s);
+  s.layer.reset();
+}
+
 void apply_more_gates(psim_peps_t& P, const psim_gate* gates, size_t n_gates) {
   psim_peps_t tmp = P;
+  for (Site& s : tmp.sites) hold_tensor(s);
   apply_gates(tmp, gates, n_gates);
   P = std::move(tmp);
 }
@@ -271,6 +279,7 @@ void project_qubit(psim_peps_t& P, int32_t qubit, int32_t value) {
   if (qubit < 0 || qubit >= P.lv * P.lh) fail(PSIM_EINVAL, "qubit out of range");
   if (value != 0 && value != 1) fail(PSIM_EINVAL, "value must be 0 or 1");
   Site& s = P.sites[(size_t)qubit];
+  hold_tensor(s);
   const size_t half = s.t.size() / 2;  // sigma is the slowest index
   std::fill(s.t.begin() + (value ? 0 : half), s.t.begin() + (value ? half : 2 * half), cd(0.0));
 }

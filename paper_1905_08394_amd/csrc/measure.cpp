@@ -32,6 +32,37 @@ void free_plan(psim_plan_t* pl);
 
 namespace psim {
 
+std::vector<cd> host_tensor(const Site& e) {
+  if (!e.layer) return e.t;
+  Site a;
+  a.dl = e.bl;
+  a.dr = e.br;
+  a.du = e.bu;
+  a.dd = e.bd;
+  const std::vector<cd>& t = *e.layer;
+  std::vector<cd> out((size_t)2 * e.dl * e.dr * e.du * e.dd, cd(0.0));
+  for (int s = 0; s < 2; ++s)
+    for (int s1 = 0; s1 < 2; ++s1)
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const cd o = e.ops[s][2 * s1 + s2];
+        if (o == cd(0.0)) continue;
+        for (int l1 = 0; l1 < a.dl; ++l1)
+          for (int r1 = 0; r1 < a.dr; ++r1)
+            for (int u1 = 0; u1 < a.du; ++u1)
+              for (int d1 = 0; d1 < a.dd; ++d1) {
+                const cd x = std::conj(t[a.at(s1, l1, r1, u1, d1)]) * o;
+                if (x == cd(0.0)) continue;
+                for (int l2 = 0; l2 < a.dl; ++l2)
+                  for (int r2 = 0; r2 < a.dr; ++r2)
+                    for (int u2 = 0; u2 < a.du; ++u2)
+                      for (int d2 = 0; d2 < a.dd; ++d2)
+                        out[e.at(s, l1 * a.dl + l2, r1 * a.dr + r2, u1 * a.du + u2, d1 * a.dd + d2)] +=
+                            x * t[a.at(s2, l2, r2, u2, d2)];
+              }
+      }
+  return out;
+}
+
 psim_peps_t* double_layer(const psim_peps_t& P, const double* ops) {
   if (!ops) fail(PSIM_EINVAL, "ops is NULL");
   const size_t n = P.sites.size();
@@ -53,28 +84,13 @@ psim_peps_t* double_layer(const psim_peps_t& P, const double* ops) {
       delete out;
       fail(PSIM_EUNSUPPORTED, "double-layer site tensor too large (" + std::to_string(legs) + " elements per slice)");
     }
-    e.t.assign(2 * legs, cd(0.0));
-    for (int s = 0; s < 2; ++s) {
-      const double* m = ops + (q * 2 + s) * 8;
-      for (int s1 = 0; s1 < 2; ++s1)
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const cd o(m[2 * (s1 * 2 + s2)], m[2 * (s1 * 2 + s2) + 1]);
-          if (o == cd(0.0)) continue;
-          for (int l1 = 0; l1 < a.dl; ++l1)
-            for (int r1 = 0; r1 < a.dr; ++r1)
-              for (int u1 = 0; u1 < a.du; ++u1)
-                for (int d1 = 0; d1 < a.dd; ++d1) {
-                  const cd x = std::conj(a.t[a.at(s1, l1, r1, u1, d1)]) * o;
-                  if (x == cd(0.0)) continue;
-                  for (int l2 = 0; l2 < a.dl; ++l2)
-                    for (int r2 = 0; r2 < a.dr; ++r2)
-                      for (int u2 = 0; u2 < a.du; ++u2)
-                        for (int d2 = 0; d2 < a.dd; ++d2)
-                          e.t[e.at(s, l1 * a.dl + l2, r1 * a.dr + r2, u1 * a.du + u2, d1 * a.dd + d2)] +=
-                              x * a.t[a.at(s2, l2, r2, u2, d2)];
-                }
-        }
-    }
+    e.bl = a.dl;
+    e.br = a.dr;
+    e.bu = a.du;
+    e.bd = a.dd;
+    e.layer = std::make_shared<const std::vector<cd>>(host_tensor(a));
+    for (int s = 0; s < 2; ++s)
+      for (int x = 0; x < 4; ++x) e.ops[s][x] = cd(ops[(q * 2 + s) * 8 + 2 * x], ops[(q * 2 + s) * 8 + 2 * x + 1]);
   }
   return out;
 }

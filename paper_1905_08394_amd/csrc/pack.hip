@@ -1,0 +1,173 @@
+// Site matrices of a plan, built on the device.
+//
+// A plan needs both projections of every site, E = A[tau] (eq. 7), as a K x N
+// matrix W[(u, l)][(d, r)] in the form its kernels read: padded, transposed,
+// expanded to reals or split, 2 to 8 times the tensor's own bytes.  Only the
+// tensors are uploaded, in one copy; one kernel finds every matrix's exponent (the
+// exact power of two that takes its largest component into [1/2, 1)) and one
+// writes every matrix into the plan's single allocation.  Sites of a
+// double-layer network are computed on the way from the layer they double
+// (measure.cpp), so their squared tensors exist nowhere else.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstring>
+
+#include "psim_internal.hpp"
+
+namespace psim {
+namespace {
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return double2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+}
+
+__device__ __forceinline__ double2 site_value(const PackSite& s, int tau, int u, int l, int d, int r) {
+  const double2* t = (const double2*)s.src;
+  if (!s.doubled)
+    return t[tau * s.stride[4] + u * s.stride[0] + l * s.stride[1] + d * s.stride[2] + r * s.stride[3]];
+  // sum_{a, b} conj(A[a]) O[a][b] A[b], the bra's legs first in every pair
+  const int u1 = u / s.base[0], l1 = l / s.base[1], d1 = d / s.base[2], r1 = r / s.base[3];
+  const long long bra = u1 * s.stride[0] + l1 * s.stride[1] + d1 * s.stride[2] + r1 * s.stride[3];
+  const long long ket = (u - u1 * s.base[0]) * s.stride[0] + (l - l1 * s.base[1]) * s.stride[1] +
+                        (d - d1 * s.base[2]) * s.stride[2] + (r - r1 * s.base[3]) * s.stride[3];
+  double2 sum = {0, 0};
+  for (int a = 0; a < 2; ++a)
+    for (int b = 0; b < 2; ++b) {
+      const double2 o = {s.ops[tau][2 * (2 * a + b)], s.ops[tau][2 * (2 * a + b) + 1]};
+      if (o.x == 0 && o.y == 0) continue;
+      const double2 x = t[a * s.stride[4] + bra];
+      const double2 v = cmul(cmul(double2{x.x, -x.y}, o), t[b * s.stride[4] + ket]);
+      sum.x += v.x;
+      sum.y += v.y;
+    }
+  return sum;
+}
+
+// W[k][n] with k = (u, l), n = (d, r)
+__device__ __forceinline__ double2 matrix_value(const PackSite& s, int tau, long long k, long long n) {
+  const int u = (int)(k / s.leg[1]), d = (int)(n / s.leg[3]);
+  return site_value(s, tau, u, (int)(k - (long long)u * s.leg[1]), d, (int)(n - (long long)d * s.leg[3]));
+}
+
+// slots[2 * site + tau]: exponent + 4096 of the largest component (0: all zeros)
+__global__ __launch_bounds__(256) void site_exponents(const PackSite* __restrict__ sites, uint32_t* slots) {
+  const PackSite& s = sites[blockIdx.y >> 1];
+  const int tau = blockIdx.y & 1;
+  const long long K = (long long)s.leg[0] * s.leg[1], N = (long long)s.leg[2] * s.leg[3];
+  double m = 0;
+  for (long long x = (long long)blockIdx.x * 256 + threadIdx.x; x < K * N; x += (long long)gridDim.x * 256) {
+    const double2 v = matrix_value(s, tau, x / N, x % N);
+    m = fmax(m, fmax(fabs(v.x), fabs(v.y)));
+  }
+  for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+  if ((threadIdx.x & 63) == 0 && m > 0) {
+    int e;
+    frexp(m, &e);
+    atomicMax(slots + blockIdx.y, (uint32_t)(e + 4096));
+  }
+}
+
+__device__ __forceinline__ void store(void* dst, int wide, long long at, double v) {
+  if (wide)
+    ((double*)dst)[at] = v;
+  else
+    ((float*)dst)[at] = (float)v;
+}
+
+// One matrix of a job, every element of its allocation (padding is zero).
+__global__ __launch_bounds__(256) void site_pack(const PackSite* __restrict__ sites, const PackJob* __restrict__ jobs,
+                                                 const uint32_t* __restrict__ slots) {
+  const PackJob& j = jobs[blockIdx.y >> 1];
+  const PackSite& s = sites[j.site];
+  const int tau = blockIdx.y & 1;
+  const uint32_t slot = slots[2 * j.site + tau];
+  const int e = slot ? (int)slot - 4096 : 0;
+  const long long K = (long long)s.leg[0] * s.leg[1], N = (long long)s.leg[2] * s.leg[3];
+  void* dst = j.dst[tau];
+  const long long total = j.rows * j.ld;  // reals; plain: complex elements
+  for (long long x = (long long)blockIdx.x * 256 + threadIdx.x; x < total; x += (long long)gridDim.x * 256) {
+    const long long row = x / j.ld, c = x - row * j.ld;
+    if (j.form == PACK_PLAIN) {
+      const double2 v = matrix_value(s, tau, row, c);
+      store(dst, j.wide, 2 * x, ldexp(v.x, -e));
+      store(dst, j.wide, 2 * x + 1, ldexp(v.y, -e));
+      continue;
+    }
+    const long long k = c >> 1, n = j.form == PACK_3M ? row : row >> 1;
+    double v = 0;
+    if (k < K && n < N) {
+      const double2 w = matrix_value(s, tau, k, n);
+      const int a = j.form == PACK_3M ? 0 : (int)(row & 1), b = (int)(c & 1);
+      // 3M: Re, Im along k; else the real expansion [[Re, -Im], [Im, Re]]
+      v = j.form == PACK_3M ? (b ? w.y : w.x) : a == b ? w.x : a ? w.y : -w.y;
+      v = ldexp(v, -e);
+    }
+    if (j.form == PACK_BF16) {  // hi plane, then lo plane, of the FP32 value
+      const float f = (float)v;
+      const __bf16 hi = (__bf16)f;
+      ((__bf16*)dst)[x] = hi;
+      ((__bf16*)dst)[total + x] = (__bf16)(f - (float)hi);
+    } else {
+      store(dst, j.wide, x, v);
+    }
+  }
+}
+
+}  // namespace
+
+// Uploads what the jobs read, runs them on the null stream and waits.  exps[2 *
+// site + tau]: the exponents taken out.
+void run_packer(SitePacker& p, std::vector<int32_t>& exps) {
+  auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t ns = p.sites.size(), nj = p.jobs.size();
+  exps.assign(2 * ns, 0);
+  if (!ns) return;
+  size_t off = al(ns * sizeof(PackSite));
+  const size_t jobs_at = off;
+  off += al(nj * sizeof(PackJob));
+  const size_t slots_at = off;
+  off += al(2 * ns * 4);
+  std::vector<size_t> at(ns);
+  int64_t most = 1, widest = 1;
+  for (size_t x = 0; x < ns; ++x) {
+    at[x] = off;
+    off += al(p.tensors[x]->size() * sizeof(cd));
+    const PackSite& s = p.sites[x];
+    most = std::max(most, (int64_t)s.leg[0] * s.leg[1] * s.leg[2] * s.leg[3]);
+  }
+  for (const PackJob& j : p.jobs) widest = std::max<int64_t>(widest, j.rows * j.ld);
+  char* d = nullptr;
+  hip_check(hipMalloc((void**)&d, off), "hipMalloc(site tensors)");
+  try {
+    std::vector<char> h(off, 0);
+    for (size_t x = 0; x < ns; ++x) {
+      p.sites[x].src = d + at[x];
+      std::memcpy(h.data() + at[x], p.tensors[x]->data(), p.tensors[x]->size() * sizeof(cd));
+    }
+    std::memcpy(h.data(), p.sites.data(), ns * sizeof(PackSite));
+    std::memcpy(h.data() + jobs_at, p.jobs.data(), nj * sizeof(PackJob));
+    hip_check(hipMemcpy(d, h.data(), off, hipMemcpyHostToDevice), "upload site tensors");
+    uint32_t* slots = (uint32_t*)(d + slots_at);
+    auto gx = [](int64_t n, size_t y) {
+      return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 1024)), (unsigned)y);
+    };
+    if (2 * std::max(ns, nj) > 65535) fail(PSIM_EUNSUPPORTED, "too many sites for one launch");
+    hipLaunchKernelGGL(site_exponents, gx(most, 2 * ns), dim3(256), 0, nullptr, (const PackSite*)d, slots);
+    hipLaunchKernelGGL(site_pack, gx(widest, 2 * nj), dim3(256), 0, nullptr, (const PackSite*)d,
+                       (const PackJob*)(d + jobs_at), slots);
+    hip_check(hipGetLastError(), "site matrix launch");
+    for (const PackJob& j : p.jobs)
+      if (j.halves)
+        for (void* q : j.dst) launch_pack_w_f16(q, q, j.rows * j.ld / 32, nullptr, j.halves == 2);
+    std::vector<uint32_t> got(2 * ns);
+    hip_check(hipMemcpy(got.data(), slots, got.size() * 4, hipMemcpyDeviceToHost), "download exponents");
+    for (size_t x = 0; x < got.size(); ++x) exps[x] = got[x] ? (int32_t)got[x] - 4096 : 0;
+  } catch (...) {
+    (void)hipFree(d);
+    throw;
+  }
+  hip_check(hipFree(d), "hipFree(site tensors)");
+}
+
+}  // namespace psim

@@ -45,6 +45,33 @@ int64_t packed_rows(int prec, int64_t N) {
   return prec == PSIM_FP32_3M ? round_up(N, 128) : round_up(2 * N, 256);
 }
 
+int SitePacker::add(const Site& s, const int order[4]) {
+  PackSite p{};
+  p.doubled = s.layer ? 1 : 0;
+  const int leg[4] = {s.dl, s.dr, s.du, s.dd};
+  const int base[4] = {p.doubled ? s.bl : s.dl, p.doubled ? s.br : s.dr, p.doubled ? s.bu : s.du,
+                       p.doubled ? s.bd : s.dd};
+  long long stride[5] = {1, 1, 1, 1, 1};  // [physical][l][r][u][d]
+  stride[2] = base[3];
+  stride[1] = stride[2] * base[2];
+  stride[0] = stride[1] * base[1];
+  for (int x = 0; x < 4; ++x) {
+    p.leg[x] = leg[order[x]];
+    p.base[x] = base[order[x]];
+    p.stride[x] = stride[order[x]];
+  }
+  p.stride[4] = stride[0] * base[0];
+  if (p.doubled)
+    for (int t = 0; t < 2; ++t)
+      for (int x = 0; x < 4; ++x) {
+        p.ops[t][2 * x] = s.ops[t][x].real();
+        p.ops[t][2 * x + 1] = s.ops[t][x].imag();
+      }
+  tensors.push_back(s.layer ? s.layer.get() : &s.t);
+  sites.push_back(p);
+  return (int)sites.size() - 1;
+}
+
 // Real expansion of a complex K x N matrix for the 4M scheme, stored
 // transposed: P[n'][k'] = B'[k'][n'] with
 //   B'[2k][2n] = Re W, B'[2k][2n+1] = Im W, B'[2k+1][2n] = -Im W, B'[2k+1][2n+1] = Re W,
@@ -145,31 +172,6 @@ void frame_sites(const psim_peps_t& P, int sweep, int R, int L, std::vector<CSit
     }
 }
 
-// W[(u, l)][(d, r)] of the projected site in the sweep frame
-void site_matrix(const psim_peps_t& P, int sweep, const CSite& c, int tau, std::vector<cd>& W) {
-  const Site& s = P.sites[c.qubit];
-  const int64_t K = (int64_t)c.du * c.dl, N = (int64_t)c.dd * c.dr;
-  W.assign((size_t)(K * N), cd(0.0));
-  for (int u = 0; u < c.du; ++u)
-    for (int l = 0; l < c.dl; ++l)
-      for (int d = 0; d < c.dd; ++d)
-        for (int r = 0; r < c.dr; ++r) {
-          // frame legs -> original legs
-          const int ol = sweep == 1 ? l : u, orr = sweep == 1 ? r : d;
-          const int ou = sweep == 1 ? u : l, od = sweep == 1 ? d : r;
-          W[(size_t)((u * c.dl + l) * N + d * c.dr + r)] = s.t[s.at(tau, ol, orr, ou, od)];
-        }
-}
-
-int exponent_of_max(const std::vector<cd>& W) {
-  double mx = 0;
-  for (const cd& w : W) mx = std::max(mx, std::max(std::abs(w.real()), std::abs(w.imag())));
-  if (mx == 0) return 0;
-  int e;
-  std::frexp(mx, &e);  // mx = f 2^e, f in [0.5, 1)
-  return e;
-}
-
 }  // namespace
 
 }  // namespace psim
@@ -242,12 +244,11 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
       if (!pl->host_only) hip_check(hipSetDevice(opts.device), "hipSetDevice");
       make_square_plan(pl, *P);
       if (!pl->host_only) {
-        hip_check(hipMalloc(&pl->d_ones, 16), "hipMalloc(ones)");
         launch_fill_ones(opts.prec, pl->d_ones, nullptr);
         hip_check(hipDeviceSynchronize(), "fill ones");
       }
     } catch (...) {
-      if (pl->d_ones) (void)hipFree(pl->d_ones);
+      if (pl->block) (void)hipFree(pl->block);
       delete pl;
       throw;
     }
@@ -488,85 +489,82 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
 
     // ---------------------------------------------------------- pack + upload
     pl->w.resize((size_t)R * L * 2);
-    std::vector<cd> W;
-    std::vector<char> buf;
+    SitePacker packer;
+    // the plan's one allocation: the scalar 1, then every matrix
+    uint64_t off = 256;
+    std::vector<uint64_t> place;  // per job and value
+    auto matrix = [&](int site, int form, int64_t rows, int64_t ld, int64_t bytes, int halves) {
+      PackJob j{};
+      j.site = site;
+      j.form = form;
+      j.rows = rows;
+      j.ld = ld;
+      j.wide = opts.prec == PSIM_FP64;
+      j.halves = halves;
+      for (int tau = 0; tau < 2; ++tau) {
+        place.push_back(off);
+        off += al((uint64_t)bytes);
+        pl->weights_bytes += (uint64_t)bytes;
+      }
+      packer.jobs.push_back(j);
+    };
+    static const int kRows[4] = {2, 0, 3, 1}, kColumns[4] = {0, 2, 1, 3};  // frame u, l, d, r of a tensor's l, r, u, d
+    const int64_t rb = opts.prec == PSIM_FP64 ? 8 : 4;
     for (int i = 0; i < R; ++i)
       for (int j = 0; j < L; ++j) {
         const CSite& c = cs(i, j);
-        for (int tau = 0; tau < 2; ++tau) {
-          DevMatrix& dm = pl->w[((size_t)i * L + j) * 2 + tau];
-          site_matrix(*P, sweep, c, tau, W);
-          dm.exp2 = exponent_of_max(W);
-          const double sc = std::ldexp(1.0, -dm.exp2);  // exact power of two
-          for (cd& x : W) x *= sc;
-          if (pl->small) {
-            dm.ld = (int64_t)c.dd * c.dr;
-            if (opts.prec == PSIM_FP64) {
-              buf.resize(W.size() * 16);
-              std::memcpy(buf.data(), W.data(), buf.size());
-            } else {
-              buf.resize(W.size() * 8);
-              float* f = reinterpret_cast<float*>(buf.data());
-              for (size_t x = 0; x < W.size(); ++x) {
-                f[2 * x] = (float)W[x].real();
-                f[2 * x + 1] = (float)W[x].imag();
-              }
-            }
-            pl->weights_bytes += buf.size();
-            if (!pl->host_only) {
-              hip_check(hipSetDevice(opts.device), "hipSetDevice");
-              hip_check(hipMalloc(&dm.ptr, buf.size()), "hipMalloc(site matrix)");
-              hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
-            }
-            continue;
-          }
-          // the last site of a row always runs the 4M transposed-store kernel
-          // in FP32 plans (its 256 x 64 tile suits the few output columns)
-          const bool last = (j == L - 1);
-          dm.f16 = pl->steps[(size_t)i * L + j].amax >= 0;
-          const int pack_prec = dm.f16 ? PSIM_FP32_3M  // split into halves below
-                                : (opts.prec == PSIM_BF16X3 || (opts.prec == PSIM_FP32_3M && last)) ? PSIM_FP32_4M
-                                                                                                    : opts.prec;
-          pack_site_matrix(pack_prec, W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld);
-          // a row cut over w reads the first site's matrix from an offset
-          // (the columns of one w chunk): 256 zero rows keep the last
-          // chunk's full tiles inside the allocation
-          if (j == 0) buf.resize(buf.size() + (size_t)256 * dm.ld * (opts.prec == PSIM_FP64 ? 8 : 4), 0);
-          pl->weights_bytes += buf.size();
-          if (!pl->host_only) {
-            hip_check(hipSetDevice(opts.device), "hipSetDevice");
-            hip_check(hipMalloc(&dm.ptr, buf.size()), "hipMalloc(site matrix)");
-            hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
-            if (dm.f16) launch_pack_w_f16(dm.ptr, dm.ptr, (int64_t)(buf.size() / 128), nullptr);
-          }
-          if (opts.prec == PSIM_BF16X3) {  // the operands of the plan's own products beside those of its companion sweep
-            if (dm.f16)
-              pack_site_matrix(PSIM_FP32_3M, W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld_b);
-            else
-              pack_site_matrix_bf16(W.data(), (int64_t)c.du * c.dl, (int64_t)c.dd * c.dr, buf, dm.ld_b, dm.plane_b);
-            pl->weights_bytes += buf.size();
-            if (!pl->host_only) {
-              hip_check(hipMalloc(&dm.ptr_b, buf.size()), "hipMalloc(site matrix)");
-              hip_check(hipMemcpy(dm.ptr_b, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
-              if (dm.f16) launch_pack_w_f16(dm.ptr_b, dm.ptr_b, (int64_t)(buf.size() / 128), nullptr, true);
-            }
-          }
+        const int64_t K = (int64_t)c.du * c.dl, N = (int64_t)c.dd * c.dr;
+        const int site = packer.add(P->sites[c.qubit], sweep == 1 ? kRows : kColumns);
+        DevMatrix* dm = &pl->w[((size_t)i * L + j) * 2];
+        if (pl->small) {
+          dm[0].ld = dm[1].ld = N;
+          matrix(site, PACK_PLAIN, K, N, K * N * pl->elem_bytes, 0);
+          continue;
+        }
+        // the last site of a row always runs the 4M transposed-store kernel
+        // in FP32 plans (its 256 x 64 tile suits the few output columns)
+        const bool f16 = pl->steps[(size_t)i * L + j].amax >= 0, bf16x3 = opts.prec == PSIM_BF16X3;
+        const int pack_prec = f16 || (opts.prec == PSIM_FP32_3M && j < L - 1) ? (int)PSIM_FP32_3M
+                              : opts.prec == PSIM_FP64                        ? (int)PSIM_FP64
+                                                                              : (int)PSIM_FP32_4M;
+        const int form = pack_prec == PSIM_FP32_3M ? PACK_3M : PACK_4M;
+        const int64_t ld = packed_ld(pack_prec, K);
+        // a row cut over w reads the first site's matrix from an offset
+        // (the columns of one w chunk): 256 zero rows keep the last
+        // chunk's full tiles inside the allocation
+        const int64_t rows = packed_rows(pack_prec, N) + (j == 0 ? 256 : 0);
+        dm[0].f16 = dm[1].f16 = f16;
+        dm[0].ld = dm[1].ld = ld;
+        matrix(site, form, rows, ld, rows * ld * rb, f16 ? 1 : 0);
+        if (bf16x3) {  // the operands of the plan's own products beside those of its companion sweep
+          dm[0].ld_b = dm[1].ld_b = ld;
+          const int64_t rows_b = packed_rows(f16 ? PSIM_FP32_3M : PSIM_FP32_4M, N);
+          if (!f16) dm[0].plane_b = dm[1].plane_b = rows_b * ld;
+          matrix(site, f16 ? PACK_3M : PACK_BF16, rows_b, ld, rows_b * ld * 4, f16 ? 2 : 0);
         }
       }
-    pl->qubit_exp.resize((size_t)2 * R * L);
-    for (size_t x = 0; x < pl->cs.size(); ++x)
-      for (int tau = 0; tau < 2; ++tau) pl->qubit_exp[2 * pl->cs[x].qubit + tau] = pl->w[2 * x + tau].exp2;
+    pl->qubit_exp.assign((size_t)2 * R * L, 0);
     if (!pl->host_only) {
-      hip_check(hipMalloc(&pl->d_ones, 16), "hipMalloc(ones)");
+      hip_check(hipSetDevice(opts.device), "hipSetDevice");
+      hip_check(hipMalloc(&pl->block, off), "hipMalloc(site matrices)");
+      pl->d_ones = pl->block;
+      for (size_t x = 0; x < packer.jobs.size(); ++x)
+        for (int tau = 0; tau < 2; ++tau) {
+          void* at = (char*)pl->block + place[2 * x + tau];
+          packer.jobs[x].dst[tau] = at;
+          DevMatrix& dm = pl->w[(size_t)2 * packer.jobs[x].site + tau];
+          (dm.ptr ? dm.ptr_b : dm.ptr) = at;
+        }
+      std::vector<int32_t> exps;
+      run_packer(packer, exps);
+      for (size_t x = 0; x < pl->cs.size(); ++x)
+        for (int tau = 0; tau < 2; ++tau)
+          pl->qubit_exp[2 * pl->cs[x].qubit + tau] = pl->w[2 * x + tau].exp2 = exps[2 * x + tau];
       launch_fill_ones(opts.prec, pl->d_ones, nullptr);
       hip_check(hipDeviceSynchronize(), "fill ones");
     }
   } catch (...) {
-    for (auto& dm : pl->w) {
-      if (dm.ptr) (void)hipFree(dm.ptr);
-      if (dm.ptr_b) (void)hipFree(dm.ptr_b);
-    }
-    if (pl->d_ones) (void)hipFree(pl->d_ones);
+    if (pl->block) (void)hipFree(pl->block);
     delete pl;
     throw;
   }
@@ -578,10 +576,6 @@ void free_plan(psim_plan_t* pl) {
   for (auto& kv : pl->graphs) (void)hipGraphExecDestroy((hipGraphExec_t)kv.second);
   if (pl->cap_stream) (void)hipStreamDestroy((hipStream_t)pl->cap_stream);
   for (void* h : pl->staging) (void)hipHostFree(h);
-  for (auto& dm : pl->w) {
-    if (dm.ptr) (void)hipFree(dm.ptr);
-    if (dm.ptr_b) (void)hipFree(dm.ptr_b);
-  }
-  if (pl->d_ones) (void)hipFree(pl->d_ones);
+  if (pl->block) (void)hipFree(pl->block);
   delete pl;
 }

@@ -27,8 +27,14 @@ void set_last_error(const std::string& msg);
 // Rank-5 site tensor A[sigma][l][r][u][d] (eq. 1), row-major in that order.
 struct Site {
   int dl = 1, dr = 1, du = 1, dd = 1;
-  std::vector<cd> t;  // 2 * dl * dr * du * dd
+  std::vector<cd> t;  // 2 * dl * dr * du * dd; empty for a doubled site
   size_t size() const { return t.size(); }
+  // Site of a double-layer network: the two slices are conj(A) O_s A of the layer
+  // A it doubles (legs bl, br, bu, bd; dl = bl^2 and so on).  Plans compute it on
+  // the device; host_tensor() gives it where the host needs it.
+  std::shared_ptr<const std::vector<cd>> layer;
+  int bl = 1, br = 1, bu = 1, bd = 1;
+  cd ops[2][4];
   size_t at(int s, int l, int r, int u, int d) const {
     return ((((size_t)s * dl + l) * dr + r) * du + u) * dd + d;
   }
@@ -50,6 +56,35 @@ bool is_two_qubit(int kind);
 
 // build.cpp
 void jacobi_svd4(const cd M[16], cd U[16], double S[4], cd V[16]);
+
+// measure.cpp: the tensor of a site, doubled or not
+std::vector<cd> host_tensor(const Site& s);
+
+// ---------------------------------------------------------------- site matrices (pack.hip)
+// A site as W[(u, l)][(d, r)] of a contraction frame: leg sizes u, l, d, r;
+// strides of those legs in the tensor it reads (doubled: the layer's), and of the
+// physical index.
+struct PackSite {
+  const void* src;
+  double ops[2][8];
+  long long stride[5];
+  int leg[4], base[4], doubled;
+};
+enum { PACK_PLAIN = 0, PACK_3M = 1, PACK_4M = 2, PACK_BF16 = 3 };
+struct PackJob {
+  void* dst[2];         // per value of the qubit
+  long long rows, ld;   // reals (plain: K x N complex elements)
+  int site, form, wide; // wide: doubles
+  int halves;           // split in place into 1: halves, 2: bfloat16 pairs (3M rows)
+};
+struct SitePacker {
+  std::vector<PackSite> sites;
+  std::vector<PackJob> jobs;
+  std::vector<const std::vector<cd>*> tensors;
+  // order: the tensor's legs (0 l, 1 r, 2 u, 3 d) that are the frame's u, l, d, r
+  int add(const Site& s, const int order[4]);
+};
+void run_packer(SitePacker& p, std::vector<int32_t>& exps);
 
 // ---------------------------------------------------------------- plan
 // Site of the swept lattice: contraction row i (0..R-1), column j (0..L-1).
@@ -86,7 +121,7 @@ struct Level {
 };
 
 struct DevMatrix {
-  void* ptr = nullptr;   // packed, on device
+  void* ptr = nullptr;   // packed, on device (inside the plan's block)
   int64_t ld = 0;        // leading dimension (real elements) of the packed layout
   int exp2 = 0;          // site matrix was scaled by 2^-exp2
   bool f16 = false;      // ptr holds W split into halves (site_f16.hip)
@@ -122,6 +157,7 @@ struct psim_plan_s {
   uint64_t ws_F = 0, ws_G = 0, ws_tab = 0, ws_total = 0;
   bool host_only = false;
   int elem_bytes = 8;
+  void* block = nullptr;                 // the one device allocation: d_ones and every site matrix
   void* d_ones = nullptr;                // device scalar 1 (the empty boundary before row 0)
   bool profile = false;                  // time launches with events
   psim_kernel_stats prof[4] = {};

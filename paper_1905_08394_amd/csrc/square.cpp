@@ -102,24 +102,9 @@ struct SquarePlan {
   uint64_t boff_tau = 0, boff_zeros = 0, boff_mx = 0, boff_desc[2] = {0, 0};
   double cmac_quads = 0, cmac_joins = 0;
   int64_t n_steps = 0;
-  ~SquarePlan() {
-    for (auto& qd : q)
-      for (auto& st : qd.s)
-        for (auto& w : st.w)
-          if (w.ptr) (void)hipFree(w.ptr);
-  }
 };
 
 namespace {
-
-int exponent_of_max_sq(const std::vector<cd>& W) {
-  double mx = 0;
-  for (const cd& w : W) mx = std::max(mx, std::max(std::abs(w.real()), std::abs(w.imag())));
-  if (mx == 0) return 0;
-  int e;
-  std::frexp(mx, &e);
-  return e;
-}
 
 // Running-tensor shapes of frame site (i, j): M, K1, K2, N as in the header.
 struct Shape {
@@ -270,37 +255,43 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
   pl->cmac = sq->cmac_quads + sq->cmac_joins;
 
   // ---------------------------------------------------------- site matrices
-  std::vector<cd> W;
-  std::vector<char> buf;
+  SitePacker packer;
+  uint64_t at = 256;  // the scalar 1, then every matrix
+  std::vector<std::pair<DevMatrix*, uint64_t>> place;
   for (auto& Q : sq->q)
-    for (auto& st : Q.s) {
-      const Site& s = P.sites[st.qubit];
+    for (size_t x = 0; x < Q.s.size(); ++x) {
+      SqSite& st = Q.s[x];
       const int64_t K = (int64_t)st.du * st.dl, N = (int64_t)st.dd * st.dr;
-      for (int tau = 0; tau < 2; ++tau) {
-        W.assign((size_t)(K * N), cd(0.0));
-        for (int u = 0; u < st.du; ++u)
-          for (int l = 0; l < st.dl; ++l)
-            for (int d = 0; d < st.dd; ++d)
-              for (int r = 0; r < st.dr; ++r) {
-                const int ol = Q.mc ? r : l, orr = Q.mc ? l : r;
-                const int ou = Q.mr ? d : u, od = Q.mr ? u : d;
-                W[(size_t)((u * st.dl + l) * N + d * st.dr + r)] = s.t[s.at(tau, ol, orr, ou, od)];
-              }
-        DevMatrix& dm = st.w[tau];
-        dm.exp2 = exponent_of_max_sq(W);
-        const double sc = std::ldexp(1.0, -dm.exp2);
-        for (cd& x : W) x *= sc;
-        const Shape sh = site_shape(Q, (int)(&st - &Q.s[0]) / Q.nc, (int)(&st - &Q.s[0]) % Q.nc);
-        dm.f16 = f16_site(prec, sh.M, sh.K1, sh.K2);
-        pack_site_matrix(dm.f16 ? (int)PSIM_FP32_3M : prec, W.data(), K, N, buf, dm.ld);
-        pl->weights_bytes += buf.size();
-        if (!pl->host_only) {
-          hip_check(hipMalloc(&dm.ptr, buf.size()), "hipMalloc(site matrix)");
-          hip_check(hipMemcpy(dm.ptr, buf.data(), buf.size(), hipMemcpyHostToDevice), "hipMemcpy(site matrix)");
-          if (dm.f16) launch_pack_w_f16(dm.ptr, dm.ptr, (int64_t)(buf.size() / 128), nullptr);
-        }
+      // the tensor's legs (l 0, r 1, u 2, d 3) that are the frame's u, l, d, r
+      const int order[4] = {Q.mr ? 3 : 2, Q.mc ? 1 : 0, Q.mr ? 2 : 3, Q.mc ? 0 : 1};
+      const Shape sh = site_shape(Q, (int)x / Q.nc, (int)x % Q.nc);
+      const bool f16 = f16_site(prec, sh.M, sh.K1, sh.K2);
+      const int pack_prec = f16 ? (int)PSIM_FP32_3M : prec;
+      PackJob j{};
+      j.site = packer.add(P.sites[st.qubit], order);
+      j.form = pack_prec == PSIM_FP32_3M ? PACK_3M : PACK_4M;
+      j.rows = packed_rows(pack_prec, N);
+      j.ld = packed_ld(pack_prec, K);
+      j.wide = prec == PSIM_FP64;
+      j.halves = f16 ? 1 : 0;
+      packer.jobs.push_back(j);
+      for (DevMatrix& dm : st.w) {
+        dm.f16 = f16;
+        dm.ld = j.ld;
+        place.emplace_back(&dm, at);
+        at += al((uint64_t)(j.rows * j.ld) * rb);
+        pl->weights_bytes += (uint64_t)(j.rows * j.ld) * rb;
       }
     }
+  if (!pl->host_only) {
+    hip_check(hipMalloc(&pl->block, at), "hipMalloc(site matrices)");
+    pl->d_ones = pl->block;
+    for (size_t x = 0; x < place.size(); ++x)
+      packer.jobs[x / 2].dst[x % 2] = place[x].first->ptr = (char*)pl->block + place[x].second;
+    std::vector<int32_t> exps;
+    run_packer(packer, exps);
+    for (size_t x = 0; x < place.size(); ++x) place[x].first->exp2 = exps[x];
+  }
   pl->sq = sq;
   pl->sq_steps = sq->n_steps;
 }
