@@ -116,14 +116,20 @@ struct Half<_Float16> {
   static __device__ __forceinline__ f32x16 mma(v8 a, v8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ void split(float a, float b, int e, float scale, v2& hi, v2& lo) {
+  static __device__ __forceinline__ v2 round(float a, float b, int e) {
     unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{ldexpf(a, e), ldexpf(b, e)}, v2));
     // hides the packed conversion from the compiler, which otherwise repeats it
     // element by element where the halves are used again
     asm("" : "+v"(u));
-    hi = __builtin_bit_cast(v2, u);
-    lo[0] = (_Float16)fmaf(a, scale, -(float)hi[0]);
-    lo[1] = (_Float16)fmaf(b, scale, -(float)hi[1]);
+    return __builtin_bit_cast(v2, u);
+  }
+  static __device__ __forceinline__ _Float16 rest(float a, float scale, _Float16 hi) {
+    return (_Float16)fmaf(a, scale, -(float)hi);
+  }
+  static __device__ __forceinline__ void split(float a, float b, int e, float scale, v2& hi, v2& lo) {
+    hi = round(a, b, e);
+    lo[0] = rest(a, scale, hi[0]);
+    lo[1] = rest(b, scale, hi[1]);
   }
 };
 
@@ -302,18 +308,23 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
 #pragma unroll
         for (int c = 0; c < 4; ++c) {  // two complex k per chunk
           const f32x4 x = *(const f32x4*)(as + r * 32 + (((4 * h + c) ^ sw) << 2));
-          typename Half<H>::v2 hr, lr, hi, li;
-          Half<H>::split(x[0], x[2], sa, scale, hr, lr);
-          Half<H>::split(x[1], x[3], sa, scale, hi, li);
+          const typename Half<H>::v2 hr = Half<H>::round(x[0], x[2], sa), hi = Half<H>::round(x[1], x[3], sa);
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             rh[2 * c + e] = hr[e];
-            rl[2 * c + e] = lr[e];
             ih[2 * c + e] = hi[e];
-            il[2 * c + e] = li[e];
+            rl[2 * c + e] = Half<H>::rest(x[2 * e], scale, hr[e]);
+            il[2 * c + e] = Half<H>::rest(x[2 * e + 1], scale, hi[e]);
           }
         }
         const v8 nh = neg(ih), nl = neg(il);
+        // Split sums: no instruction moves across the block of products.  Left
+        // alone, the scheduler spreads the split of A and the wait for the next
+        // stage between them, and each then holds up the products behind it:
+        // 5x5 (1+40+1), 16 sharing a prefix, 225 -> 185 ms (0.97 -> 1.2 PFLOP/s);
+        // (1+32+1) 3M, 256 bitstrings, 326 -> 287 ms.  Without partial sums three
+        // workgroups per CU fill such gaps (6x6 (1+24+1): 11.1 ms, 11.2 fenced).
+        if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int bj = 0; bj < NBLK; ++bj) {
           PSIM_MM(rl, w[bj][0], dst[bi][bj][0]);
@@ -344,6 +355,7 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
           PSIM_MM(nh, w[bj][2], dst[bi][bj][0]);
           PSIM_MM(ih, w[bj][0], dst[bi][bj][1]);
         }
+        if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);
       } else {
 #pragma unroll
         for (int g = 0; g < 2; ++g) {  // 8 k each: an instruction sums their Re and Im products
