@@ -205,6 +205,7 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
     int64_t ld = 0, ld_b = 0, plane_b = 0;
     const bool aligned = (uintptr_t)dA % 16 == 0 && (batch == 1 || a_batch_stride % 2 == 0);
     const bool f16 = !transpose_out && aligned && f16_site(prec, M, K1, K2);
+    const bool first = !transpose_out && aligned && first_site(prec, M, K1, K2);
     int w_exp = 0;
     if (f16 && prec != PSIM_BF16X3) {  // the halves hold components below 1
       double mx = 0;
@@ -214,8 +215,8 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
       if (mx > 0) std::frexp(mx, &w_exp);
       for (cd& w : Wc) w = cd(std::ldexp(w.real(), -w_exp), std::ldexp(w.imag(), -w_exp));
     }
-    pack_site_matrix(f16 ? PSIM_FP32_3M : prec == PSIM_BF16X3 ? PSIM_FP32_4M : prec, Wc.data(), K, N, packed, ld);
-    if (prec == PSIM_BF16X3 && !f16) pack_site_matrix_bf16(Wc.data(), K, N, packed_b, ld_b, plane_b);
+    pack_site_matrix(f16 || first ? PSIM_FP32_3M : prec == PSIM_BF16X3 ? PSIM_FP32_4M : prec, Wc.data(), K, N, packed, ld);
+    if (prec == PSIM_BF16X3 && !f16 && !first) pack_site_matrix_bf16(Wc.data(), K, N, packed_b, ld_b, plane_b);
     void* dW = nullptr;
     void* dWb = nullptr;
     hip_check(hipMalloc(&dW, packed.size() + packed_b.size() + (f16 ? (size_t)batch * 4 : 0)), "hipMalloc(W)");
@@ -246,6 +247,7 @@ psim_status psim_contract_site(int32_t prec, int64_t batch, int64_t M, int64_t K
       g.trans_out = transpose_out ? 1 : 0;
       g.split = split;
       g.cfg = transpose_out ? 0 : cfg;
+      if (first) g.f16 = 3;
       if (f16) {
         launch_pack_w_f16(dW, dW, (int64_t)(packed.size() / 128), st, prec == PSIM_BF16X3);
         g.f16 = prec == PSIM_BF16X3 ? 2 : 1;

@@ -373,7 +373,6 @@ void prepare(psim_plan_t* pl, const std::vector<uint64_t>& key, const std::vecto
       }
       continue;
     }
-    const int64_t rows_per_col = (prec == PSIM_FP32_3M) ? 1 : 2;  // packed rows per complex column (first site)
     for (int64_t g0 = 0; g0 < nodes; g0 += lev.group) {
       const int64_t gn = std::min<int64_t>(lev.group, nodes - g0);
       for (int v0 = 0; v0 < lev.Dv; v0 += c) {
@@ -419,6 +418,7 @@ void prepare(psim_plan_t* pl, const std::vector<uint64_t>& key, const std::vecto
               a_exp = 0;
               a_max = g.amax_out;
             } else {
+              if (s.first) g.f16 = 3;
               a_exp += growth_exp(s.K1 * s.K2);
             }
             g.tau = W.tau[i] + g0 * L + j;
@@ -481,6 +481,7 @@ void prepare(psim_plan_t* pl, const std::vector<uint64_t>& key, const std::vecto
               // the columns (w, r_0) of the w chunk: packed rows from w0 * dr on;
               // results stored per (w, v) pair as [w][v][m][r_0]
               const int64_t dr = pl->cs[(size_t)i * L].dr;
+              const int rows_per_col = s.first || prec == PSIM_FP32_3M ? 1 : 2;  // packed rows per complex column
               const uint64_t off = (uint64_t)w0 * dr * rows_per_col * w0m.ld * (prec == PSIM_FP64 ? 8 : 4);
               g.W0 = (const char*)w0m.ptr + off;
               g.W1 = (const char*)w1m.ptr + off;

@@ -357,6 +357,8 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
         pl->small = false;
     for (Step& st : pl->steps)  // largest components of the f16 sites' outputs
       if (!pl->small && st.kind == 1 && f16_site(opts.prec, st.M, st.K1, st.K2)) st.amax = pl->n_amax++;
+    for (Step& st : pl->steps)
+      st.first = !pl->small && st.kind == 0 && first_site(opts.prec, st.M, st.K1, st.K2);
     tab += (uint64_t)pl->n_amax * al((uint64_t)nmax_all * 4);
     pl->ws_tab = tab;
     if (tab + Fmin[0] + Fmin[1] > budget)
@@ -524,7 +526,8 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
         // the last site of a row always runs the 4M transposed-store kernel
         // in FP32 plans (its 256 x 64 tile suits the few output columns)
         const bool f16 = pl->steps[(size_t)i * L + j].amax >= 0, bf16x3 = opts.prec == PSIM_BF16X3;
-        const int pack_prec = f16 || (opts.prec == PSIM_FP32_3M && j < L - 1) ? (int)PSIM_FP32_3M
+        const bool first = pl->steps[(size_t)i * L + j].first;
+        const int pack_prec = f16 || first || (opts.prec == PSIM_FP32_3M && j < L - 1) ? (int)PSIM_FP32_3M
                               : opts.prec == PSIM_FP64                        ? (int)PSIM_FP64
                                                                               : (int)PSIM_FP32_4M;
         const int form = pack_prec == PSIM_FP32_3M ? PACK_3M : PACK_4M;
@@ -534,6 +537,7 @@ psim_plan_t* make_plan(const psim_peps_t* P, const psim_plan_opts* o) {
         // chunk's full tiles inside the allocation
         const int64_t rows = packed_rows(pack_prec, N) + (j == 0 ? 256 : 0);
         dm[0].f16 = dm[1].f16 = f16;
+        dm[0].first = dm[1].first = first;
         dm[0].ld = dm[1].ld = ld;
         matrix(site, form, rows, ld, rows * ld * rb, f16 ? 1 : 0);
         if (bf16x3) {  // the operands of the plan's own products beside those of its companion sweep

@@ -101,6 +101,7 @@ struct Step {
   int64_t M = 1, K1 = 1, K2 = 1, N = 1;
   int64_t g_out = 0;     // elements of the output per (node, v) (kind 0/1)
   int cfg = 0;           // kernel tile candidate chosen by the tuner
+  bool first = false;    // kind 0 on the first-site kernel (first_site)
   int amax = -1;         // f16 sites: index of the workspace slots for the largest component of the output
 };
 
@@ -125,6 +126,7 @@ struct DevMatrix {
   int64_t ld = 0;        // leading dimension (real elements) of the packed layout
   int exp2 = 0;          // site matrix was scaled by 2^-exp2
   bool f16 = false;      // ptr holds W split into halves (site_f16.hip)
+  bool first = false;    // ptr is packed for the first-site kernel (3M rows)
   void* ptr_b = nullptr; // BF16x3 plans: f16 sites: W split into bfloat16 pairs; others: hi and lo bf16 planes of
   int64_t ld_b = 0, plane_b = 0;  // the 4M expansion
 };
@@ -265,7 +267,8 @@ struct GemmLaunch {
   const void* Wb1 = nullptr;
   int64_t ldwb = 0, planeb = 0;
   int64_t ldct = 0;                   // transposed stores: row stride of C^T in complex elements (0 = M)
-  int32_t f16 = 0;                    // W0 and W1 are split into 1: halves (FP32), 2: bfloat16 pairs (BF16x3); site_f16.hip
+  int32_t f16 = 0;                    // W0 and W1 are split into 1: halves (FP32), 2: bfloat16 pairs (BF16x3);
+                                      // 3: 3M rows for the first-site kernel; site_f16.hip
   int32_t a_exp = 0, w_exp = 0;       // f16: |components of A| < 2^a_exp (times what amax_in says), W is 2^-w_exp
                                       // times the matrix to contract
   const uint32_t* amax_in = nullptr;  // f16, per node: exponent + 4096 of the largest component of A (0: A is zero)
@@ -292,6 +295,8 @@ void launch_site_gemm(const GemmLaunch& g, void* stream);
 // contraction goes there when its matrix was packed for it, which f16_site
 // decides from the shape alone (M: the most rows it is launched with).
 bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2);
+// the same for first sites of a row (K2 = 1, plain or blocked stores)
+bool first_site(int prec, int64_t M, int64_t K1, int64_t K2);
 void launch_site_f16(const GemmLaunch& g, void* stream);
 int group_variant_f16(const GemmLaunch& g, void* out, long long* tiles);
 void launch_group_f16(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream);

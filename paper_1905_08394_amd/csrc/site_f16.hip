@@ -86,6 +86,7 @@ struct F16Args {
   long long ldw;             // bytes between rows of W
   long long sA_node, sA_v, sC_node, sC_v;
   long long MT, NT, T;
+  long long nb, sCw;         // first sites: see GemmLaunch
   int Bz, nst, a_exp, w_exp;
 };
 
@@ -459,24 +460,180 @@ struct F16Group {
   int nprob;
 };
 
-template <typename H, int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
-__global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16_group(F16Group ga) {
+// The problem that owns this workgroup's tile and its number there, or -1.
+__device__ __forceinline__ long long group_tile(const F16Group& ga, F16Args& p) {
   const long long total = ga.start[ga.nprob];
   const long long per_xcd = (total + 7) / 8;
   const long long g = (long long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (g >= total) return;
+  if (g >= total) return -1;
   int lo = 0, hi = ga.nprob - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (ga.start[mid] <= g) lo = mid; else hi = mid - 1;
   }
   lo = __builtin_amdgcn_readfirstlane(lo);
-  F16Args p;
   const int* src = (const int*)ga.probs[lo];
   int* dst = (int*)&p;
 #pragma unroll
   for (int w = 0; w < (int)(sizeof(F16Args) / 4); ++w) dst[w] = __builtin_amdgcn_readfirstlane(src[w]);
-  site_f16_body<H, WVM, WVN, MBLK, NBLK, SPLIT>(p, g - ga.start[lo]);
+  return g - ga.start[lo];
+}
+
+template <typename H, int WVM, int WVN, int MBLK, int NBLK, bool SPLIT, int OCC>
+__global__ __launch_bounds__(64 * WVM * WVN, OCC) void site_f16_group(F16Group ga) {
+  F16Args p;
+  const long long t = group_tile(ga, p);
+  if (t >= 0) site_f16_body<H, WVM, WVN, MBLK, NBLK, SPLIT>(p, t);
+}
+
+// First sites of a row (K2 = 1, A[k][m]): FP32 products, FP32 sums, for every
+// precision but FP64.  Each output takes few products (K = one bond) and the
+// output is the row's largest tensor, so the time is that of writing it.  An A
+// stage (8 k of 128 m, 1 KB each) goes to LDS as it lies and is read with m
+// across the lanes; Re and Im have an accumulator each, so a lane stores whole
+// complex numbers, 256 bytes to a row.  The K-major form of the general kernel
+// turned A round on its way through registers with conflicting 4-byte LDS
+// stores and wrote 4 bytes a lane.  The products and their order are that
+// form's (4M): the results are the same bit for bit.
+// 5x5 (1+32+1), 256 bitstrings: BF16x3 52 -> 25 ms, FP32 3M 30 -> 25 (about 100
+// GB written: 4 TB/s); 6x6 (1+24+1) 2.6 -> 1.0 ms; bond 32 (K = 32, 5x5
+// (1+40+1)) 2.98 -> 3.01 ms a launch, where the products take as long as the
+// writes.
+template <bool SPLIT>
+__device__ __forceinline__ void site_first_body(const F16Args& p, const long long t) {
+  constexpr int BM = 128, BN = 64, BK = 8;
+  __shared__ __attribute__((aligned(1024))) float sA0[BM * BK * 2], sA1[BM * BK * 2];
+  __shared__ __attribute__((aligned(1024))) float sB0[BN * BK * 2], sB1[BN * BK * 2];
+
+  const long long nt = t % p.NT;
+  const long long rest = t / p.NT;
+  const long long mt = rest % p.MT;
+  const long long z = rest / p.MT;
+  const long long node = z / p.Bz, vb = z % p.Bz;
+  const long long ablk = p.a_index ? (long long)p.a_index[node] : node;
+  const float* __restrict__ A = p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
+  const int tauv = p.tau ? (int)p.tau[node * p.tau_stride] : 0;
+  const char* __restrict__ W = (const char*)(tauv ? p.W1 : p.W0);
+  float* __restrict__ C = p.C + 2 * (node * p.sC_node + vb * p.sC_v);
+  const long long m0 = mt * BM, n0 = nt * BN;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+
+  // A: wave copy `it` is row 4 it + wid of the stage, two m per lane (M even).
+  // W: rows of 64 bytes (8 complex k), 16 rows per wave, physical chunk lane % 4
+  // from logical (lane % 4) ^ (row / 2) % 4.
+  const char* a_src = (const char*)(A + 2 * (wid * p.M + min(m0 + 2 * lane, p.M - 2)));
+  const int brow = wid * 16 + (lane >> 2);
+  const char* b_src = W + min(n0 + brow, p.N - 1) * p.ldw + (((lane & 3) ^ (brow >> 1)) & 3) * 16;
+  const long long a_step = 4 * p.M * 8;
+  auto issue = [&](float* da, float* db) {
+    __builtin_amdgcn_global_load_lds((const void*)a_src, PSIM_LDS(da + wid * 256), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(a_src + a_step), PSIM_LDS(da + (4 + wid) * 256), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)b_src, PSIM_LDS(db + wid * 256), 16, 0, 0);
+    a_src += 2 * a_step;
+    b_src += 64;
+  };
+
+  f32x16 acc[2][2], part[SPLIT ? 2 : 1][2];
+#pragma unroll
+  for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[bj][q][r] = 0;
+
+  const int frow = lane & 31, h = lane >> 5;
+  // open, close: first and last stage of a partial sum (16 k)
+  auto compute = [&](const float* as, const float* bs, const bool open, const bool close) {
+    if (SPLIT && open) {
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) part[SPLIT ? bj : 0][q][r] = 0;
+    }
+    auto& dst = [&]() -> auto& {
+      if constexpr (SPLIT) return part;
+      else return acc;
+    }();
+#pragma unroll
+    for (int g = 0; g < BK / 4; ++g) {  // lane half h: k 4g + 2h and the next
+      f32x2 a[2];
+      f32x4 w[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) a[c] = *(const f32x2*)(as + (4 * g + 2 * h + c) * 256 + 2 * (wid * 32 + frow));
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj) {
+        const int r = bj * 32 + frow;
+        w[bj] = *(const f32x4*)(bs + r * 16 + (((2 * g + h) ^ (r >> 1)) & 3) * 4);
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj) {
+          dst[bj][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][0], w[bj][2 * c], dst[bj][0], 0, 0, 0);
+          dst[bj][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][0], w[bj][2 * c + 1], dst[bj][1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj) {
+          dst[bj][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][1], -w[bj][2 * c + 1], dst[bj][0], 0, 0, 0);
+          dst[bj][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][1], w[bj][2 * c], dst[bj][1], 0, 0, 0);
+        }
+      }
+    }
+    if (SPLIT && close) {
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) acc[bj][q] += part[SPLIT ? bj : 0][q];
+    }
+  };
+  constexpr unsigned kWaitVm0 = 0x3f70;
+
+  issue(sA0, sB0);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __syncthreads();
+  const int nst = p.nst;
+  int s = 0;
+  for (; s + 1 < nst; s += 2) {
+    issue(sA1, sB1);
+    compute(sA0, sB0, true, false);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+    if (s + 2 < nst) issue(sA0, sB0);
+    compute(sA1, sB1, false, true);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+  }
+  if (s < nst) compute(sA0, sB0, true, true);
+
+#pragma unroll
+  for (int bj = 0; bj < 2; ++bj) {
+    const long long col = n0 + bj * 32 + frow;
+    if (col >= p.N) continue;
+    // plain rows, or blocks of nb columns
+    float* dst = C + 2 * (p.nb ? (col / p.nb) * p.sCw + col % p.nb : col);
+    const long long ld = p.nb ? p.nb : p.N;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const long long row = m0 + wid * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (row < p.M) *(f32x2*)(dst + 2 * row * ld) = f32x2{acc[bj][0][r], acc[bj][1][r]};
+    }
+  }
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(256, SPLIT ? 3 : 4) void site_first(F16Args p) {
+  const long long per_xcd = (p.T + 7) / 8;
+  const long long t = (long long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t < p.T) site_first_body<SPLIT>(p, t);
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(256, SPLIT ? 3 : 4) void site_first_group(F16Group ga) {
+  F16Args p;
+  const long long t = group_tile(ga, p);
+  if (t >= 0) site_first_body<SPLIT>(p, t);
 }
 
 // Packed FP32 rows (Re, Im interleaved along k, groups of 16 complex k = 128
@@ -565,12 +722,20 @@ bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2) {
          (K2 % 16 == 0 || 16 % K2 == 0) && (K2 < 16 ? M < (1 << 24) : K2 < (1 << 21)) && K1 * K2 < (1 << 21);
 }
 
+// Whole stages of 8 k, read as 16-byte chunks of two m.
+bool first_site(int prec, int64_t M, int64_t K1, int64_t K2) {
+  return prec != PSIM_FP64 && K2 == 1 && K1 % 8 == 0 && M % 2 == 0 && K1 < (1 << 21);
+}
+
 // Tiles: every form has the same products in the same order for each output.
 //   0: 128 x 128 complex outputs, 4 waves of 64 x 64, two workgroups per CU
 //   1: 128 x 64, 4 waves of 32 x 64, three workgroups per CU
 //   2: the same with partial sums, two workgroups per CU
 //   3, 4: 0 and 1 for BF16x3
+//   5, 6: first sites, 128 x 64, without and with partial sums (up to 16 k there
+//   is one partial sum, the result itself)
 static int f16_variant(const GemmLaunch& g) {
+  if (g.f16 == 3) return g.split && g.K1 > 16 ? 6 : 5;
   if (g.split && g.f16 == 1) return 2;
   const long long big = ((g.M + 127) / 128) * ((g.N + 127) / 128) * g.nodes * g.Bz;
   return (g.N % 128 == 0 && big >= 1024 ? 0 : 1) + (g.f16 == 2 ? 3 : 0);
@@ -579,7 +744,8 @@ static int f16_variant(const GemmLaunch& g) {
 static F16Args f16_args(const GemmLaunch& g, int variant) {
   if (g.M < 1 || g.K1 < 1 || g.K2 < 1 || g.N < 1 || g.nodes < 1 || g.Bz < 1)
     fail(PSIM_EINVAL, "site gemm: non-positive size");
-  if (!f16_site(g.prec, g.M, g.K1, g.K2) || g.trans_out || g.nb || g.beta || (uintptr_t)g.A % 16 || g.sA_node % 2 ||
+  const bool first = g.f16 == 3;
+  if (!(first ? first_site(g.prec, g.M, g.K1, g.K2) : !g.nb && f16_site(g.prec, g.M, g.K1, g.K2)) || g.trans_out || g.beta || (uintptr_t)g.A % 16 || g.sA_node % 2 ||
       g.sA_v % 2 || g.ldw >= (1 << 23))
     fail(PSIM_EINTERNAL, "site gemm: shape or alignment the half-precision kernels do not take");
   F16Args a{};
@@ -602,10 +768,12 @@ static F16Args f16_args(const GemmLaunch& g, int variant) {
   a.sC_node = g.sC_node;
   a.sC_v = g.sC_v;
   a.Bz = g.Bz;
-  a.nst = (int)(g.K1 * g.K2 / 16);
+  a.nb = g.nb;
+  a.sCw = g.sCw;
+  a.nst = (int)(g.K1 * g.K2 / (first ? 8 : 16));
   a.a_exp = g.a_exp;
   a.w_exp = g.w_exp;
-  const int bn = variant % 3 == 0 ? 128 : 64;
+  const int bn = variant == 0 || variant == 3 ? 128 : 64;
   a.MT = (a.M + 127) / 128;
   a.NT = (a.N + bn - 1) / bn;
   a.T = a.MT * a.NT * g.nodes * g.Bz;
@@ -624,7 +792,9 @@ void launch_site_f16(const GemmLaunch& g, void* stream) {
     case 1: hipLaunchKernelGGL((site_f16<_Float16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
     case 2: hipLaunchKernelGGL((site_f16<_Float16, 4, 1, 1, 2, true, 2>), grid, wg, 0, st, a); break;
     case 3: hipLaunchKernelGGL((site_f16<__bf16, 2, 2, 2, 2, false, 2>), grid, wg, 0, st, a); break;
-    default: hipLaunchKernelGGL((site_f16<__bf16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((site_f16<__bf16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((site_first<false>), grid, wg, 0, st, a); break;
+    default: hipLaunchKernelGGL((site_first<true>), grid, wg, 0, st, a); break;
   }
   hip_check(hipGetLastError(), "site_f16 launch");
 }
@@ -641,7 +811,7 @@ int group_variant_f16(const GemmLaunch& g, void* out, long long* tiles) {
 
 void launch_group_f16(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  if (nprob < 1 || nprob > kMaxProbs || variant < 0 || variant > 4) fail(PSIM_EINTERNAL, "bad f16 group");
+  if (nprob < 1 || nprob > kMaxProbs || variant < 0 || variant > 6) fail(PSIM_EINTERNAL, "bad f16 group");
   F16Group ga{};
   for (int i = 0; i < nprob; ++i) {
     ga.probs[i] = (const F16Args*)d_probs[i];
@@ -658,7 +828,9 @@ void launch_group_f16(int variant, const void* const* d_probs, const long long* 
     case 1: hipLaunchKernelGGL((site_f16_group<_Float16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
     case 2: hipLaunchKernelGGL((site_f16_group<_Float16, 4, 1, 1, 2, true, 2>), grid, wg, 0, st, ga); break;
     case 3: hipLaunchKernelGGL((site_f16_group<__bf16, 2, 2, 2, 2, false, 2>), grid, wg, 0, st, ga); break;
-    default: hipLaunchKernelGGL((site_f16_group<__bf16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
+    case 4: hipLaunchKernelGGL((site_f16_group<__bf16, 4, 1, 1, 2, false, 3>), grid, wg, 0, st, ga); break;
+    case 5: hipLaunchKernelGGL((site_first_group<false>), grid, wg, 0, st, ga); break;
+    default: hipLaunchKernelGGL((site_first_group<true>), grid, wg, 0, st, ga); break;
   }
   hip_check(hipGetLastError(), "grouped site_f16 launch");
 }

@@ -266,7 +266,8 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
       const int order[4] = {Q.mr ? 3 : 2, Q.mc ? 1 : 0, Q.mr ? 2 : 3, Q.mc ? 0 : 1};
       const Shape sh = site_shape(Q, (int)x / Q.nc, (int)x % Q.nc);
       const bool f16 = f16_site(prec, sh.M, sh.K1, sh.K2);
-      const int pack_prec = f16 ? (int)PSIM_FP32_3M : prec;
+      const bool first = first_site(prec, sh.M, sh.K1, sh.K2);
+      const int pack_prec = f16 || first ? (int)PSIM_FP32_3M : prec;
       PackJob j{};
       j.site = packer.add(P.sites[st.qubit], order);
       j.form = pack_prec == PSIM_FP32_3M ? PACK_3M : PACK_4M;
@@ -277,6 +278,7 @@ void make_square_plan(psim_plan_t* pl, const psim_peps_t& P) {
       packer.jobs.push_back(j);
       for (DevMatrix& dm : st.w) {
         dm.f16 = f16;
+        dm.first = first;
         dm.ld = j.ld;
         place.emplace_back(&dm, at);
         at += al((uint64_t)(j.rows * j.ld) * rb);
@@ -462,6 +464,7 @@ struct SqRun {
   }
   void bound_site(GemmLaunch& g, const DevMatrix& w, size_t site, Bound& b) {
     if (!w.f16) {
+      if (w.first) g.f16 = 3;
       b.exp += growth_exp(g.K1 * g.K2);
       return;
     }
