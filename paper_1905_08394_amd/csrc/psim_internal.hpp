@@ -297,7 +297,10 @@ void launch_site_gemm(const GemmLaunch& g, void* stream);
 bool f16_site(int prec, int64_t M, int64_t K1, int64_t K2);
 // the same for first sites of a row (K2 = 1, plain or blocked stores)
 bool first_site(int prec, int64_t M, int64_t K1, int64_t K2);
+// last sites of a row (transposed stores of up to 32 columns, the 4M packing)
+bool last_site(const GemmLaunch& g);
 void launch_site_f16(const GemmLaunch& g, void* stream);
+void launch_site_last(const GemmLaunch& g, void* stream);
 int group_variant_f16(const GemmLaunch& g, void* out, long long* tiles);
 void launch_group_f16(int variant, const void* const* d_probs, const long long* start, int nprob, void* stream);
 int f16_descriptor_bytes();

@@ -87,7 +87,8 @@ struct F16Args {
   long long sA_node, sA_v, sC_node, sC_v;
   long long MT, NT, T;
   long long nb, sCw;         // first sites: see GemmLaunch
-  int Bz, nst, a_exp, w_exp;
+  long long ldct;            // last sites: row stride of C^T
+  int Bz, nst, a_exp, w_exp, beta;
 };
 
 constexpr int kTop = 15;     // A is scaled to below 2^kTop,
@@ -636,6 +637,147 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 4) void site_first_group(F16Group 
   if (t >= 0) site_first_body<SPLIT>(p, t);
 }
 
+// Last sites of a row (transposed stores, up to 32 output columns): FP32 4M
+// products on the real expansion of W.  The row's largest tensor is read once
+// and its result is small, so the time is that of reading it, if no matrix
+// instruction works on padding: tiles are 32 NBLK reals (16 or 32 complex
+// columns) wide, 128 m high, one wave to 32 m.  A and W stages (rows of 16
+// complex k) go to LDS without registers.  The blocks hold C^T, so lanes run
+// along m and store whole complex numbers.  Products and order are those of the
+// general kernel: the results are the same bit for bit.
+// 5x5 (1+32+1), 256 bitstrings: 30 -> 20 ms FP32 3M, 30 -> 23 ms BF16x3 (100 GB
+// read: 5 TB/s); 6x6 (1+24+1) 1.4 -> 1.1 ms; 32 columns (bond 32): 7.7 -> 7.1 ms.
+template <int NBLK, bool SPLIT>
+__global__ __launch_bounds__(256, NBLK == 1 ? 4 : 3) void site_last(F16Args p) {
+  constexpr int BM = 128, BN = 32 * NBLK;
+  __shared__ __attribute__((aligned(1024))) float sA0[BM * 32], sA1[BM * 32];
+  __shared__ __attribute__((aligned(1024))) float sB0[BN * 32], sB1[BN * 32];
+
+  const long long per_xcd = (p.T + 7) / 8;
+  const long long t = (long long)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t >= p.T) return;
+  const long long mt = t % p.MT;
+  const long long z = t / p.MT;
+  const long long node = z / p.Bz, vb = z % p.Bz;
+  const long long ablk = p.a_index ? (long long)p.a_index[node] : node;
+  const float* __restrict__ A = p.A + 2 * (ablk * p.sA_node + vb * p.sA_v);
+  const int tauv = p.tau ? (int)p.tau[node * p.tau_stride] : 0;
+  const char* __restrict__ W = (const char*)(tauv ? p.W1 : p.W0);
+  float* __restrict__ C = p.C + 2 * (node * p.sC_node + vb * p.sC_v);
+  const long long m0 = mt * BM;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const long long sK1 = p.M * p.K2;
+  const int K2 = (int)p.K2;
+
+  // copies as in site_f16_body; W rows past the last column repeat it
+  unsigned aoff[4], boff[NBLK];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int row = (it * 4 + wid) * 8 + (lane >> 3);
+    const int kc = 2 * ((lane & 7) ^ swz(row));
+    const long long r = min((long long)row, p.M - 1 - m0);
+    const int q = K2 < 16 ? kc / K2 : 0;
+    aoff[it] = (unsigned)((q * sK1 + r * K2 + (kc - q * K2)) * 8);
+  }
+#pragma unroll
+  for (int it = 0; it < NBLK; ++it) {
+    const int row = (it * 4 + wid) * 8 + (lane >> 3);
+    boff[it] = (unsigned)(min((long long)row, 2 * p.N - 1) * p.ldw) + (unsigned)((lane & 7) ^ swz(row)) * 16u;
+  }
+  const char* abase = (const char*)(A + 2 * m0 * p.K2);
+  const char* bbase = W;
+  const long long a_k1 = sK1 * 8 * (K2 < 16 ? 16 / K2 : 1);
+  int fk2 = 0;
+  auto issue = [&](float* da, float* db) {
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+      __builtin_amdgcn_global_load_lds((const void*)(abase + aoff[it]), PSIM_LDS(da + (it * 4 + wid) * 256), 16, 0, 0);
+#pragma unroll
+    for (int it = 0; it < NBLK; ++it)
+      __builtin_amdgcn_global_load_lds((const void*)(bbase + boff[it]), PSIM_LDS(db + (it * 4 + wid) * 256), 16, 0, 0);
+    bbase += 128;
+    fk2 += 16;
+    if (fk2 >= K2) {
+      abase += a_k1 - (long long)(fk2 - 16) * 8;
+      fk2 = 0;
+    } else {
+      abase += 128;
+    }
+  };
+
+  f32x16 acc[NBLK];
+#pragma unroll
+  for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[bj][r] = 0;
+  const int frow = lane & 31, h = lane >> 5;
+  auto compute = [&](const float* as, const float* bs) {
+    f32x16 part[SPLIT ? NBLK : 1];
+    if (SPLIT) {
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[SPLIT ? bj : 0][r] = 0;
+    }
+    auto& dst = [&]() -> auto& {
+      if constexpr (SPLIT) return part;
+      else return acc;
+    }();
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {  // 8 reals: lane half h reads 8g + 4h .. 8g + 4h + 3
+      const int ra = wid * 32 + frow;
+      const f32x4 a = *(const f32x4*)(as + ra * 32 + (((2 * g + h) ^ swz(ra)) << 2));
+      f32x4 w[NBLK];
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) {
+        const int r = bj * 32 + frow;
+        w[bj] = *(const f32x4*)(bs + r * 32 + (((2 * g + h) ^ swz(r)) << 2));
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int bj = 0; bj < NBLK; ++bj)
+          dst[bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[bj][e], a[e], dst[bj], 0, 0, 0);
+    }
+    if (SPLIT) {
+#pragma unroll
+      for (int bj = 0; bj < NBLK; ++bj) acc[bj] += part[SPLIT ? bj : 0];
+    }
+  };
+  constexpr unsigned kWaitVm0 = 0x3f70;
+
+  issue(sA0, sB0);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __syncthreads();
+  const int nst = p.nst;
+  int s = 0;
+  for (; s + 1 < nst; s += 2) {
+    issue(sA1, sB1);
+    compute(sA0, sB0);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+    if (s + 2 < nst) issue(sA0, sB0);
+    compute(sA1, sB1);
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+  }
+  if (s < nst) compute(sA0, sB0);
+
+  const long long m = m0 + wid * 32 + frow;
+  if (m >= p.M) return;
+#pragma unroll
+  for (int bj = 0; bj < NBLK; ++bj)
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const int n = (bj * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) >> 1;
+      if (n >= p.N) continue;
+      f32x2* dst = (f32x2*)(C + 2 * (n * p.ldct + m));
+      f32x2 v = {acc[bj][r], acc[bj][r + 1]};
+      if (p.beta) v += *dst;
+      *dst = v;
+    }
+}
+
 // Packed FP32 rows (Re, Im interleaved along k, groups of 16 complex k = 128
 // bytes) to halves of the same 16 k, scaled by 2^kTopW: Re hi, Re lo, Im hi, Im
 // lo; or to bfloat16: all hi, all lo, Re and Im in turn.  One thread per group,
@@ -797,6 +939,47 @@ void launch_site_f16(const GemmLaunch& g, void* stream) {
     default: hipLaunchKernelGGL((site_first<true>), grid, wg, 0, st, a); break;
   }
   hip_check(hipGetLastError(), "site_f16 launch");
+}
+
+// The stages are f16_site's, the columns fit one tile, and every 16-byte copy is
+// aligned.
+bool last_site(const GemmLaunch& g) {
+  return g.trans_out && g.N <= 32 && g.prec != PSIM_FP32_3M && f16_site(g.prec, g.M, g.K1, g.K2) &&
+         (uintptr_t)g.A % 16 == 0 && g.sA_node % 2 == 0 && g.sA_v % 2 == 0 && g.w_koff % 2 == 0 && g.ldw < (1 << 23) && !g.nb;
+}
+
+void launch_site_last(const GemmLaunch& g, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  F16Args a{};
+  a.A = (const float*)g.A;
+  a.C = (float*)g.C;
+  a.W0 = (const float*)g.W0 + 2 * g.w_koff;
+  a.W1 = (const float*)(g.W1 ? g.W1 : g.W0) + 2 * g.w_koff;
+  a.a_index = g.a_index;
+  a.tau = g.tau;
+  a.tau_stride = g.tau_stride;
+  a.M = g.M;
+  a.K2 = g.K2;
+  a.N = g.N;
+  a.ldw = g.ldw * 4;
+  a.sA_node = g.sA_node;
+  a.sA_v = g.sA_v;
+  a.sC_node = g.sC_node;
+  a.sC_v = g.sC_v;
+  a.ldct = g.ldct ? g.ldct : g.M;
+  a.beta = g.beta;
+  a.Bz = g.Bz;
+  a.nst = (int)(g.K1 * g.K2 / 16);
+  a.MT = (a.M + 127) / 128;
+  a.T = a.MT * g.nodes * g.Bz;
+  const long long blocks = (a.T + 7) / 8 * 8;
+  if (blocks > 0x7fffffffLL) fail(PSIM_EUNSUPPORTED, "grid too large");
+  const dim3 grid((unsigned)blocks), wg(256);
+  if (g.N <= 16)
+    hipLaunchKernelGGL((g.split ? site_last<1, true> : site_last<1, false>), grid, wg, 0, st, a);
+  else
+    hipLaunchKernelGGL((g.split ? site_last<2, true> : site_last<2, false>), grid, wg, 0, st, a);
+  hip_check(hipGetLastError(), "site_last launch");
 }
 
 int f16_descriptor_bytes() { return (int)sizeof(F16Args); }
