@@ -878,9 +878,10 @@ def main():
         "config": {"workload": f"{args.lattice}x{args.lattice} lattice, random circuit depth (1+{args.depth}+1), "
                                f"D={stats['chi']}, exact row-scheme amplitudes of {len(bits)} bitstrings "
                                f"sharing rows 1-{args.lattice - 1} (last-row variants)",
-                   "precision": {"fp32": "complex64 storage, FP32 operands split in two halves, FP32 sums (MFMA)",
+                   "precision": {"fp32": "complex64 storage, FP32 operands split in two halves, FP32 sums (MFMA; first "
+                                         "and last sites of a row FP32)",
                                  "fp32_3m": "complex64 storage, FP32 operands split in two halves, FP32 sums "
-                                            "(MFMA; first sites of a row FP32 3M)" +
+                                            "(MFMA; first and last sites of a row FP32)" +
                                             (", split K accumulation (partial sums)" if split_on else ""),
                                  "fp64": "complex128 storage, FP64 MFMA",
                                  "bf16x3": "complex64 storage, BF16 hi/lo split, 3 BF16 MFMA products, "

@@ -189,7 +189,8 @@ namespace {
 // spread row loses what it gains once the batch fills the chip (5x5 (1+16+1):
 // 64 bitstrings 277 -> 178 us, 1024 1070 -> 1050 us, 4096 3.58 -> 3.70 ms), so
 // those plans are bounded by their work.  The FP64 buffers hold half as many
-// elements.  BF16x3 plans keep their own products.
+// elements.  BF16x3 plans keep their own products.  (Whole calls, both sides with
+// the host's share of the time; a later change took 50 to 150 us off either.)
 bool small_network(psim_plan_t& pl) {
   const int prec = pl.opts.prec, R = pl.R, L = pl.L;
   if (prec == PSIM_BF16X3 || L < 2 || L > kSmallL) return false;
