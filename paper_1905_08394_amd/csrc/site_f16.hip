@@ -40,7 +40,7 @@
 // absolute) precision: their error stays below 2^-40 of the largest.
 //
 // Measured (ms before, FP32 units -> now): 16 x (M = 32768, K = N = 1024) split
-// 26.3 -> 13.5, unsplit 23.9 -> 11.0; 64 x (4096, 256, 256) split 0.95 -> 0.49,
+// 26.3 -> 12.8, unsplit 23.9 -> 11.0; 64 x (4096, 256, 256) split 0.95 -> 0.47,
 // unsplit 0.89 -> 0.40; 512 x (4096, 64, 64) split 0.81 -> 0.43 (HBM: 5.0
 // TB/s), unsplit 0.68 -> 0.40; 4 x (4096, 4096, 4096) unsplit 12.0 -> 5.7.
 //
@@ -54,6 +54,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cstdint>
 #include <cstring>
 
@@ -88,7 +89,7 @@ struct F16Args {
   long long MT, NT, T;
   long long nb, sCw;         // first sites: see GemmLaunch
   long long ldct;            // last sites: row stride of C^T
-  int Bz, nst, a_exp, w_exp, beta;
+  int Bz, nst, a_exp, w_exp, beta, stream;
 };
 
 constexpr int kTop = 15;     // A is scaled to below 2^kTop,
@@ -179,6 +180,20 @@ __device__ __forceinline__ void raise_exponent(float m, uint32_t* slot) {
     const uint32_t x = (uint32_t)(e + 4096);
     if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < x) atomicMax(slot, x);
   }
+}
+
+// One complex number of an output, past the caches or not.  A launch whose output
+// outgrows the 256 MB cache behind the L2s leaves nothing there that its reader
+// finds, but pushes out the operands that other tiles share: 5x5 (1+32+1), 256
+// bitstrings, FP32 3M 273 -> 262 ms, BF16x3 242 -> 234, 6x6 (1+24+1), 64, 9.35 ->
+// 9.02 ms.  Smaller outputs are read from the cache by the next site (6x6
+// (1+24+1), 8, BF16x3: 1.30 ms, 1.44 with streaming stores).
+template <bool STREAM>
+__device__ __forceinline__ void put(float* dst, const f32x2 v) {
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, (f32x2*)dst);
+  else
+    *(f32x2*)dst = v;
 }
 
 #define PSIM_LDS(p) ((__attribute__((address_space(3))) void*)(p))
@@ -426,20 +441,26 @@ __device__ __forceinline__ void site_f16_body(const F16Args& p, const long long 
 
   const int sc = PLANAR ? p.w_exp - sa - kTopW : p.w_exp;
   float mx = 0;
+  auto store = [&](auto stream) {
 #pragma unroll
-  for (int bi = 0; bi < MBLK; ++bi)
+    for (int bi = 0; bi < MBLK; ++bi)
 #pragma unroll
-    for (int bj = 0; bj < NBLK; ++bj)
+      for (int bj = 0; bj < NBLK; ++bj)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const long long row = m0 + (wr * MBLK + bi) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        const long long col = nt * BN + (wc * NBLK + bj) * 32 + frow;
-        if (row < p.M && col < p.N) {
-          const f32x2 v = {ldexpf(acc[bi][bj][0][r], sc), ldexpf(acc[bi][bj][1][r], sc)};
-          mx = fmaxf(mx, fmaxf(fabsf(v[0]), fabsf(v[1])));
-          *(f32x2*)(C + 2 * (row * p.N + col)) = v;
+        for (int r = 0; r < 16; ++r) {
+          const long long row = m0 + (wr * MBLK + bi) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+          const long long col = nt * BN + (wc * NBLK + bj) * 32 + frow;
+          if (row < p.M && col < p.N) {
+            const f32x2 v = {ldexpf(acc[bi][bj][0][r], sc), ldexpf(acc[bi][bj][1][r], sc)};
+            mx = fmaxf(mx, fmaxf(fabsf(v[0]), fabsf(v[1])));
+            put<stream.value>(C + 2 * (row * p.N + col), v);
+          }
         }
-      }
+  };
+  if (p.stream)
+    store(std::true_type{});
+  else
+    store(std::false_type{});
   if (p.amax_out) raise_exponent(mx, p.amax_out + node);
 }
 
@@ -608,19 +629,25 @@ __device__ __forceinline__ void site_first_body(const F16Args& p, const long lon
   }
   if (s < nst) compute(sA0, sB0, true, true);
 
+  auto store = [&](auto stream) {
 #pragma unroll
-  for (int bj = 0; bj < 2; ++bj) {
-    const long long col = n0 + bj * 32 + frow;
-    if (col >= p.N) continue;
-    // plain rows, or blocks of nb columns
-    float* dst = C + 2 * (p.nb ? (col / p.nb) * p.sCw + col % p.nb : col);
-    const long long ld = p.nb ? p.nb : p.N;
+    for (int bj = 0; bj < 2; ++bj) {
+      const long long col = n0 + bj * 32 + frow;
+      if (col >= p.N) continue;
+      // plain rows, or blocks of nb columns
+      float* dst = C + 2 * (p.nb ? (col / p.nb) * p.sCw + col % p.nb : col);
+      const long long ld = p.nb ? p.nb : p.N;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const long long row = m0 + wid * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (row < p.M) *(f32x2*)(dst + 2 * row * ld) = f32x2{acc[bj][0][r], acc[bj][1][r]};
+      for (int r = 0; r < 16; ++r) {
+        const long long row = m0 + wid * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (row < p.M) put<stream.value>(dst + 2 * row * ld, f32x2{acc[bj][0][r], acc[bj][1][r]});
+      }
     }
-  }
+  };
+  if (p.stream)
+    store(std::true_type{});
+  else
+    store(std::false_type{});
 }
 
 template <bool SPLIT>
@@ -645,8 +672,8 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 4) void site_first_group(F16Group 
 // complex k) go to LDS without registers.  The blocks hold C^T, so lanes run
 // along m and store whole complex numbers.  Products and order are those of the
 // general kernel: the results are the same bit for bit.
-// 5x5 (1+32+1), 256 bitstrings: 30 -> 20 ms FP32 3M, 30 -> 23 ms BF16x3 (100 GB
-// read: 5 TB/s); 6x6 (1+24+1) 1.4 -> 1.1 ms; 32 columns (bond 32): 7.7 -> 7.1 ms.
+// 5x5 (1+32+1), 256 bitstrings: 30 -> 22 ms (100 GB read: 4.6 TB/s); 6x6
+// (1+24+1) 1.4 -> 1.0 ms; 32 columns (bond 32, 5x5 (1+40+1)) 7.7 -> 6.8 ms.
 template <int NBLK, bool SPLIT>
 __global__ __launch_bounds__(256, NBLK == 1 ? 4 : 3) void site_last(F16Args p) {
   constexpr int BM = 128, BN = 32 * NBLK;
@@ -910,6 +937,7 @@ static F16Args f16_args(const GemmLaunch& g, int variant) {
   a.sC_node = g.sC_node;
   a.sC_v = g.sC_v;
   a.Bz = g.Bz;
+  a.stream = g.M * g.N * g.nodes * g.Bz > (1 << 25);  // 256 MB of complex64
   a.nb = g.nb;
   a.sCw = g.sCw;
   a.nst = (int)(g.K1 * g.K2 / (first ? 8 : 16));
